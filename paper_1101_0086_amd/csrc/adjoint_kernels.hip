@@ -58,18 +58,17 @@ __device__ __forceinline__ long long wrap(long long g, long long n) {
     return g;
 }
 
-// node-precision transform, double-buffered when DB (as block_fft_db), its
-// twiddles read from the LDS table `twl` in each pass (block_fft_warm,
-// TW_TABLE: the values of the B-point table, the arithmetic of block_fft)
+// node-precision transform, double-buffered when DB, its twiddles read from
+// the LDS table `twl` in each pass
 template <typename T, int B, int SG, bool DB>
 __device__ __forceinline__ void node_fft(cx<T> (&v)[PTS], cx<T>*& db0, cx<T>*& db1, cx<T>* lds,
                                          const cx<T>* __restrict__ tw, const cx<T>* twl, int tid) {
     if constexpr (DB) {
-        block_fft_warm<T, B, PTS, SG, true, TW_TABLE>(v, db0, db1, tw, tid, twl);
+        block_fft<T, B, SG, true, TW_TABLE>(v, db0, db1, tw, tid, nullptr, twl);
     } else {
         cx<T>* l0 = lds;
         cx<T>* l1 = lds;
-        block_fft_warm<T, B, PTS, SG, false, TW_TABLE>(v, l0, l1, tw, tid, twl);
+        block_fft<T, B, SG, false, TW_TABLE>(v, l0, l1, tw, tid, nullptr, twl);
     }
 }
 
@@ -105,8 +104,8 @@ mpa_adjoint_block_kernel(const cx<T>* __restrict__ fin, const cx<double>* __rest
                          const cx<T>* __restrict__ tw, const cx<double>* __restrict__ tw64,
                          const double* __restrict__ taper, const cx<double>* __restrict__ mask_grad, int M,
                          const double* __restrict__ nw, double out_scale, double w1) {
-    __shared__ cx<double> lds64[lds_elems<B>()];
-    __shared__ cx<T> twl[tl_elems(B)];
+    __shared__ cx<double> lds64[B];
+    __shared__ cx<T> twl[tl_elems<T>(B)];
     fill_twiddle_table<T, B>(twl, tw, threadIdx.x, B / PTS);   // barrier: each item's first
     cx<T>* __restrict__ store = node_store + (size_t)blockIdx.x * NIT * M * 3 * B;
     cx<double>* __restrict__ last = last_store + (size_t)blockIdx.x * B;

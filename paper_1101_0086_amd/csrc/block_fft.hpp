@@ -1,7 +1,7 @@
 // Workgroup-wide power-of-two FFT held in registers, exchanged through LDS.
 //
-// A workgroup of NT = B / R threads transforms B points; thread `tid` holds
-// the R points with index tid + NT * m (m = 0..R-1) in registers, both before
+// A workgroup of NT = B / 8 threads transforms B points; thread `tid` holds
+// the 8 points with index tid + NT * m (m = 0..7) in registers, both before
 // and after the transform.  Every array indexed by frequency (spectra,
 // running sums, phase factors) can therefore stay in the registers of the
 // thread that owns those frequencies for the whole long step.
@@ -10,9 +10,22 @@
 // and span p (product of the earlier radices) reads x[i + q B / r] for
 // butterfly i (q = 0..r-1), multiplies by w^(q k), k = i mod p,
 // w = exp(SIGN 2 pi i / (p r)), takes an r-point DFT and writes
-// y[(i - k) r + k + q p].  The first pass reads registers, the last pass
-// writes registers (its output index set is again tid + NT m), the passes in
-// between exchange through LDS.  Results come out in natural order.
+// y[(i - k) r + k + q p].  The first pass (radix 8, or the remainder
+// 2^(log2 B mod 3)) has no twiddles and reads registers, the others are
+// radix 8 with one butterfly per thread, the last writes registers (its
+// output index set is again tid + NT m), the passes in between exchange
+// through LDS.  Results come out in natural order.
+//
+// A radix-8 pass with twiddles is three levels of radix-2 butterflies
+// a +- t b, the twiddle inside the butterfly: s = a + t b is four fused
+// multiply-adds, a - t b = 2 a - s two more.  With w = w^k of the pass the
+// levels use t = w^4; w^2 and i w^2; w, e^{i pi/4} w, i w and e^{3 i pi/4} w
+// (conjugated for SIGN = -1), so a pass takes 72 operations and four stored
+// twiddles (w, w^2, w^4, e^{i pi/4} w) where seven complex products in front
+// of an 8-point DFT take 80 and seven.
+// Rounding, 4096 points, rms relative error against long double: 1.34e-7 in
+// FP32 (1.19e-7 with products of table twiddles), 2.7e-16 in FP64 (4.0e-16
+// with the seven twiddles formed from one table load).
 //
 // SIGN = +1 is the transform with kernel exp(+i omega t) (the paper's F),
 // SIGN = -1 its unnormalised inverse.
@@ -44,9 +57,6 @@ __device__ __forceinline__ int lds_slot(int j) {
         return j ^ ((j >> 3) & 7);
     }
 }
-
-template <int B>
-constexpr int lds_elems() { return B + B / 8; }
 
 // ---- small DFTs in registers (output in natural order, in place) ----------
 
@@ -105,169 +115,46 @@ __device__ __forceinline__ void dft(cx<T> (&x)[r]) {
     }
 }
 
-// ---- one Stockham pass ------------------------------------------------------
-
-template <typename T, int B, int R, int r, int p, int SIGN, bool FROM_LDS, bool TO_LDS, bool COLD>
-__device__ __forceinline__ void fft_pass(cx<T> (&v)[R], cx<T>* lds,
-                                         const cx<T>* __restrict__ tw, int tid) {
-    constexpr int NT = B / R;
-    constexpr int NB = R / r;   // butterflies per thread in this pass
-    if constexpr (FROM_LDS) {
-        __syncthreads();        // the previous pass's writes are visible
-#pragma unroll
-        for (int m = 0; m < R; ++m) v[m] = lds[lds_slot<T>(tid + NT * m)];
-        __syncthreads();        // every read done before this pass overwrites
-    }
-#pragma unroll
-    for (int u = 0; u < NB; ++u) {
-        const int i = tid + u * NT;
-        int k = i & (p - 1);
-        if constexpr (COLD) asm volatile("" : "+v"(k));   // twiddles loaded here, not kept live
-        cx<T> x[r];
-#pragma unroll
-        for (int q = 0; q < r; ++q) x[q] = v[u + q * NB];
-        if constexpr (p > 1) {
-            constexpr int stride = B / (p * r);
-#pragma unroll
-            for (int q = 1; q < r; ++q) {
-                cx<T> w = tw[q * k * stride];   // exp(+2 pi i q k / (p r))
-                if constexpr (SIGN < 0) w.im = -w.im;
-                x[q] = cmul(x[q], w);
-            }
-        }
-        dft<SIGN, r>(x);
-        if constexpr (TO_LDS) {
-            const int base = (i - k) * r + k;
-#pragma unroll
-            for (int q = 0; q < r; ++q) lds[lds_slot<T>(base + q * p)] = x[q];
-        } else {
-#pragma unroll
-            for (int q = 0; q < r; ++q) v[u + q * NB] = x[q];
-        }
-    }
+// a, b = a + t b, a - t b with t = w (SIGN = +1) or conj(w) (SIGN = -1)
+template <int SIGN, typename T>
+__device__ __forceinline__ void bfly(cx<T>& a, cx<T>& b, cx<T> w) {
+    const T wi = SIGN > 0 ? w.im : -w.im;
+    const cx<T> s = {fma(-wi, b.im, fma(w.re, b.re, a.re)), fma(wi, b.re, fma(w.re, b.im, a.im))};
+    b = {fma(T(2), a.re, -s.re), fma(T(2), a.im, -s.im)};
+    a = s;
 }
 
-// Radix of the pass whose span is P: the first pass takes the remainder
-// 2^(log2 B mod 3) when B is not a power of 8, every other pass is radix 8.
-template <int B, int P>
-constexpr int pass_radix() {
-    if constexpr (P == 1) {
-        constexpr int rem = ilog2(B) % 3;
-        return rem == 0 ? 8 : (1 << rem);
-    } else {
-        return 8;
-    }
+// Twiddles of one radix-8 pass for one thread: w = exp(2 pi i k / (8 p)),
+// w^2, w^4 and e^{i pi/4} w.
+template <typename T>
+struct PassTw {
+    cx<T> w1, w2, w4, w8;
+};
+
+// 8-point DFT of x_q w^q (see the file comment), output in natural order.
+template <int SIGN, typename T>
+__device__ __forceinline__ void dft8_tw(cx<T> (&x)[8], const PassTw<T>& w) {
+    const cx<T> iw2 = {-w.w2.im, w.w2.re}, iw1 = {-w.w1.im, w.w1.re}, iw8 = {-w.w8.im, w.w8.re};
+    bfly<SIGN>(x[0], x[4], w.w4);
+    bfly<SIGN>(x[2], x[6], w.w4);
+    bfly<SIGN>(x[1], x[5], w.w4);
+    bfly<SIGN>(x[3], x[7], w.w4);
+    bfly<SIGN>(x[0], x[2], w.w2);
+    bfly<SIGN>(x[4], x[6], iw2);
+    bfly<SIGN>(x[1], x[3], w.w2);
+    bfly<SIGN>(x[5], x[7], iw2);
+    bfly<SIGN>(x[0], x[1], w.w1);      // X_0, X_4
+    bfly<SIGN>(x[4], x[5], w.w8);      // X_1, X_5
+    bfly<SIGN>(x[2], x[3], iw1);       // X_2, X_6
+    bfly<SIGN>(x[6], x[7], iw8);       // X_3, X_7
+    const cx<T> x1 = x[4], x3 = x[6], x4 = x[1], x6 = x[3];
+    x[1] = x1;
+    x[3] = x3;
+    x[4] = x4;
+    x[6] = x6;
 }
 
-template <typename T, int B, int R, int SIGN, int P, bool COLD>
-__device__ __forceinline__ void fft_from(cx<T> (&v)[R], cx<T>* lds,
-                                         const cx<T>* __restrict__ tw, int tid) {
-    constexpr int r = pass_radix<B, P>();
-    constexpr bool first = (P == 1);
-    constexpr bool last = (P * r == B);
-    static_assert(R % r == 0, "points per thread must be a multiple of every radix");
-    fft_pass<T, B, R, r, P, SIGN, !first, !last, COLD>(v, lds, tw, tid);
-    if constexpr (!last) fft_from<T, B, R, SIGN, P * r, COLD>(v, lds, tw, tid);
-}
-
-// ---- double-buffered variant ---------------------------------------------------
-// Passes alternate between two LDS buffers: pass s writes buf[s % 2] and pass
-// s + 1 reads it after one barrier.  The barrier after the reads is not
-// needed, since the next write goes to the other buffer, whose last readers
-// passed the barrier before this read.  A call ends having read
-// buf[(E - 1) % 2] (E exchanges); the caller's next call must start writing
-// the other buffer, so for odd E the two pointers are swapped on return.
-template <typename T, int B, int R, int r, int p, int SIGN, bool FROM_LDS, bool TO_LDS, bool COLD>
-__device__ __forceinline__ void fft_pass_db(cx<T> (&v)[R], const cx<T>* lds_in, cx<T>* lds_out,
-                                            const cx<T>* __restrict__ tw, int tid) {
-    constexpr int NT = B / R;
-    constexpr int NB = R / r;
-    if constexpr (FROM_LDS) {
-        __syncthreads();        // the previous pass's writes are visible
-#pragma unroll
-        for (int m = 0; m < R; ++m) v[m] = lds_in[lds_slot<T>(tid + NT * m)];
-    }
-#pragma unroll
-    for (int u = 0; u < NB; ++u) {
-        const int i = tid + u * NT;
-        int k = i & (p - 1);
-        if constexpr (COLD) asm volatile("" : "+v"(k));   // twiddles loaded here, not kept live
-        cx<T> x[r];
-#pragma unroll
-        for (int q = 0; q < r; ++q) x[q] = v[u + q * NB];
-        if constexpr (p > 1) {
-            constexpr int stride = B / (p * r);
-#pragma unroll
-            for (int q = 1; q < r; ++q) {
-                cx<T> w = tw[q * k * stride];
-                if constexpr (SIGN < 0) w.im = -w.im;
-                x[q] = cmul(x[q], w);
-            }
-        }
-        dft<SIGN, r>(x);
-        if constexpr (TO_LDS) {
-            const int base = (i - k) * r + k;
-#pragma unroll
-            for (int q = 0; q < r; ++q) lds_out[lds_slot<T>(base + q * p)] = x[q];
-        } else {
-#pragma unroll
-            for (int q = 0; q < r; ++q) v[u + q * NB] = x[q];
-        }
-    }
-}
-
-template <typename T, int B, int R, int SIGN, int P, int S, bool COLD>
-__device__ __forceinline__ void fft_from_db(cx<T> (&v)[R], cx<T>* buf0, cx<T>* buf1,
-                                            const cx<T>* __restrict__ tw, int tid) {
-    constexpr int r = pass_radix<B, P>();
-    constexpr bool first = (P == 1);
-    constexpr bool last = (P * r == B);
-    // pass S reads buf[(S - 1) % 2] and writes buf[S % 2]
-    cx<T>* in = (S % 2) ? buf0 : buf1;
-    cx<T>* out = (S % 2) ? buf1 : buf0;
-    fft_pass_db<T, B, R, r, P, SIGN, !first, !last, COLD>(v, in, out, tw, tid);
-    if constexpr (!last) fft_from_db<T, B, R, SIGN, P * r, S + 1, COLD>(v, buf0, buf1, tw, tid);
-}
-
-template <int B, int P>
-constexpr int exchanges() {
-    constexpr int r = pass_radix<B, P>();
-    if constexpr (P * r == B) return 0;
-    else return 1 + exchanges<B, P * r>();
-}
-
-// B-point transform through two LDS buffers (each lds_elems<B>() elements);
-// see fft_pass_db.  Every LDS access made before the call must have passed
-// a barrier if it touched either buffer.  COLD as for block_fft.
-template <typename T, int B, int R, int SIGN, bool COLD = false>
-__device__ __forceinline__ void block_fft_db(cx<T> (&v)[R], cx<T>*& buf0, cx<T>*& buf1,
-                                             const cx<T>* __restrict__ tw, int tid) {
-    static_assert((B & (B - 1)) == 0 && B >= 64, "power-of-two block");
-    fft_from_db<T, B, R, SIGN, 1, 0, COLD>(v, buf0, buf1, tw, tid);
-    if constexpr (exchanges<B, 1>() % 2 == 1) {
-        cx<T>* t = buf0;
-        buf0 = buf1;
-        buf1 = t;
-    }
-}
-
-// ---- variant with the twiddles formed from one load per pass ------------------
-// For transforms outside the node loop (the FP64 carry transforms).  Passes
-// after the first are radix 8 with one butterfly per thread, which needs
-// w^k, w^{2k}, ..., w^{7k} (w = exp(2 pi i / (8 p))): each pass loads w^k
-// alone and forms the other six by complex products (w^2 = w w, w^3 = w^2 w,
-// w^4 = w^2 w^2, w^5 = w^4 w, w^6 = w^4 w^2, w^7 = w^4 w^3; at most four
-// roundings deep, a few units in the last place): seven table loads per
-// pass, gathered through the vector memory path, cost more than the six
-// products.  TW_AHEAD: the twiddles of every pass are formed when the call
-// begins (their latency paid once); TW_PASS: at the start of each pass
-// (fewer registers); either way they do not stay in registers after the
-// call, and the arithmetic is the same.  TW_TABLE: read from a table in LDS
-// (fill_twiddle_table), the B-point table's own values, as block_fft uses
-// them, for transforms inside a loop whose registers cannot hold them.
-// DBUF selects the exchange of block_fft_db (two buffers) or of block_fft
-// (one).
-enum TwiddleSource { TW_AHEAD = 0, TW_PASS = 1, TW_TABLE = 2 };
+// ---- passes --------------------------------------------------------------------
 
 constexpr int first_radix(int B) { return ilog2(B) % 3 == 0 ? 8 : (1 << (ilog2(B) % 3)); }
 
@@ -281,157 +168,188 @@ constexpr int n_passes(int B) {
 // span of pass s (s = 0: the first)
 constexpr int pass_span(int B, int s) { return s == 0 ? 1 : first_radix(B) * (1 << (3 * (s - 1))); }
 
-// w^{q k}, q = 1..7, of pass S (S >= 1) for this thread
+// Where the twiddles of the passes come from; the values are the same.
+//   TW_REGS   the caller's registers (load_twiddles once per kernel): node
+//             transforms, whose loop has the registers (24 at 4096 points, FP32)
+//   TW_AHEAD  loads from the B-point table two passes ahead of their use:
+//             transforms outside the node loop (all of them loaded when the call
+//             begins, FP64, cost 40 spilled registers there)
+//   TW_PASS   loads at the start of each pass (fewer registers)
+//   TW_TABLE  a table in LDS (fill_twiddle_table), read at the start of each
+//             pass: transforms inside a loop whose registers cannot hold them
+//   TW_TABLE_LEAN  the same, the LDS addresses formed in each call (about 90
+//             integer operations at 4096 points) instead of being kept across
+//             the caller's loop: callers that spill otherwise
+enum TwiddleSource { TW_REGS = 0, TW_AHEAD = 1, TW_PASS = 2, TW_TABLE = 3, TW_TABLE_LEAN = 4 };
+
+// e^{i pi/4} w: from the table in FP32, formed from w in FP64 (three 16-byte
+// loads per pass instead of four, and an LDS table that fits beside two
+// 4096-point exchange buffers).
+template <typename T>
+constexpr int tw_loads() { return sizeof(T) == 4 ? 4 : 3; }
+
+template <typename T>
+__device__ __forceinline__ cx<T> eighth(cx<T> w) {
+    const T h = T(0.70710678118654752440084436210484903928);
+    return {h * (w.re - w.im), h * (w.re + w.im)};
+}
+
+// pass S (S >= 1) of a B-point transform, from the B-point table `tw`
 template <typename T, int B, int S>
-__device__ __forceinline__ void pass_twiddles(cx<T> (&w)[7], const cx<T>* __restrict__ tw, int tid) {
+__device__ __forceinline__ void pass_twiddles(PassTw<T>& w, const cx<T>* __restrict__ tw, int tid) {
     constexpr int p = pass_span(B, S);
     constexpr int stride = B / (p * 8);
     const int k = tid & (p - 1);
-    const cx<T> w1 = tw[k * stride];
-    const cx<T> w2 = cmul(w1, w1);
-    const cx<T> w3 = cmul(w2, w1);
-    const cx<T> w4 = cmul(w2, w2);
-    w[0] = w1;
-    w[1] = w2;
-    w[2] = w3;
-    w[3] = w4;
-    w[4] = cmul(w4, w1);
-    w[5] = cmul(w4, w2);
-    w[6] = cmul(w4, w3);
+    w.w1 = tw[k * stride];
+    w.w2 = tw[2 * k * stride];
+    w.w4 = tw[4 * k * stride];
+    if constexpr (tw_loads<T>() == 4) w.w8 = tw[(k + p) * stride];
+    else w.w8 = eighth(w.w1);
 }
 
-// LDS twiddle table of the radix-8 passes: pass s >= 1 (span p) holds
-// w^{q k} = tw[q k B / (8 p)] for q = 1..7, k < p at tl_offset(B, s) +
-// (q - 1) p + k, so that the lanes of a pass, whose k are consecutive, read
-// consecutive entries.
+// LDS twiddle table: pass s >= 1 (span p) holds w, w^2, w^4 and, in FP32,
+// e^{i pi/4} w, p entries each, at tl_offset(s), so that the lanes of a pass,
+// whose k are consecutive, read consecutive entries.
+template <typename T>
 constexpr int tl_offset(int B, int s) {
     int o = 0;
-    for (int t = 1; t < s; ++t) o += 7 * pass_span(B, t);
+    for (int t = 1; t < s; ++t) o += tw_loads<T>() * pass_span(B, t);
     return o;
 }
 
-constexpr int tl_elems(int B) { return tl_offset(B, n_passes(B)); }
+template <typename T>
+constexpr int tl_elems(int B) { return tl_offset<T>(B, n_passes(B)); }
 
 // Fills the table from the B-point table `tw`, `nthreads` threads striding
 // over it; the caller puts a barrier between this and the first transform.
 template <typename T, int B>
 __device__ __forceinline__ void fill_twiddle_table(cx<T>* tl, const cx<T>* __restrict__ tw, int tid, int nthreads) {
     constexpr int NP = n_passes(B);
-    for (int e = tid; e < tl_elems(B); e += nthreads) {
+    for (int e = tid; e < tl_elems<T>(B); e += nthreads) {
         int s = 1;
-        while (s + 1 < NP && e >= tl_offset(B, s + 1)) ++s;
+        while (s + 1 < NP && e >= tl_offset<T>(B, s + 1)) ++s;
         const int p = pass_span(B, s);
-        const int r = e - tl_offset(B, s);
-        const int q = r / p + 1, k = r - (q - 1) * p;
-        tl[e] = tw[q * k * (B / (8 * p))];
+        const int r = e - tl_offset<T>(B, s);
+        const int q = r / p, k = r - q * p;
+        tl[e] = tw[(q == 3 ? k + p : (k << q)) * (B / (8 * p))];
     }
 }
 
 template <typename T, int B, int S, int NP>
-__device__ __forceinline__ void all_twiddles(cx<T> (&w)[NP - 1][7], const cx<T>* __restrict__ tw, int tid) {
+__device__ __forceinline__ void all_twiddles(PassTw<T> (&w)[NP - 1], const cx<T>* __restrict__ tw, int tid) {
     if constexpr (S < NP) {
         pass_twiddles<T, B, S>(w[S - 1], tw, tid);
         all_twiddles<T, B, S + 1, NP>(w, tw, tid);
     }
 }
 
-template <typename T, int B, int R, int SIGN, int S, int NP, bool DBUF, int TWS>
-__device__ __forceinline__ void passes_warm(cx<T> (&v)[R], cx<T>* buf0, cx<T>* buf1, const cx<T> (&wall)[NP - 1][7],
-                                            const cx<T>* __restrict__ tw, const cx<T>* tl, int tid) {
-    constexpr int NT = B / R;
+// twiddles of every pass for TW_REGS
+template <typename T, int B>
+struct Twiddles {
+    PassTw<T> w[n_passes(B) - 1];
+};
+
+template <typename T, int B>
+__device__ __forceinline__ void load_twiddles(Twiddles<T, B>& t, const cx<T>* __restrict__ tw, int tid) {
+    all_twiddles<T, B, 1, n_passes(B)>(t.w, tw, tid);
+}
+
+template <typename T, int B, int SIGN, int S, int NP, bool DBUF, int TWS>
+__device__ __forceinline__ void passes(cx<T> (&v)[8], cx<T>* buf0, cx<T>* buf1, PassTw<T> (&wall)[NP - 1],
+                                       const cx<T>* __restrict__ tw, const cx<T>* tl, int tid) {
+    if constexpr (TWS == TW_AHEAD) {
+        int t = tid;
+        asm volatile("" : "+v"(t));          // loaded here, not earlier
+        if constexpr (S == 0) pass_twiddles<T, B, 1>(wall[0], tw, t);
+        if constexpr (S + 2 < NP) pass_twiddles<T, B, S + 2>(wall[S + 1], tw, t);
+    }
+    constexpr int NT = B / 8;
     constexpr int p = pass_span(B, S);
-    constexpr int r = S == 0 ? first_radix(B) : 8;
-    constexpr int NB = R / r;
     constexpr bool first = (S == 0), last = (S == NP - 1);
     // exchange buffers: alternating (DBUF, pass S reads buf[(S - 1) % 2] and
     // writes buf[S % 2]) or one
     cx<T>* in = DBUF ? ((S % 2) ? buf0 : buf1) : buf0;
     cx<T>* out = DBUF ? ((S % 2) ? buf1 : buf0) : buf0;
-    if constexpr (!first) {
-        __syncthreads();
+    if constexpr (first) {
+        constexpr int r = first_radix(B);
+        constexpr int NB = 8 / r;
 #pragma unroll
-        for (int m = 0; m < R; ++m) v[m] = in[lds_slot<T>(tid + NT * m)];
-        if constexpr (!DBUF) __syncthreads();
-    }
-    cx<T> wp[7];
-    if constexpr (!first) {
-        if constexpr (TWS == TW_AHEAD) {
+        for (int u = 0; u < NB; ++u) {
+            cx<T> x[r];
 #pragma unroll
-            for (int q = 0; q < 7; ++q) wp[q] = wall[S - 1][q];
+            for (int q = 0; q < r; ++q) x[q] = v[u + q * NB];
+            dft<SIGN, r>(x);
+            const int base = (tid + u * NT) * r;
+#pragma unroll
+            for (int q = 0; q < r; ++q) out[lds_slot<T>(base + q)] = x[q];
+        }
+    } else {
+        __syncthreads();        // the previous pass's writes are visible
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            constexpr int order[8] = {0, 4, 2, 6, 1, 5, 3, 7};   // the order the butterflies take them in
+            v[order[q]] = in[lds_slot<T>(tid + NT * order[q])];
+        }
+        if constexpr (!DBUF) __syncthreads();   // every read done before this pass overwrites
+        PassTw<T> w;
+        if constexpr (TWS == TW_REGS || TWS == TW_AHEAD) {
+            w = wall[S - 1];
         } else if constexpr (TWS == TW_PASS) {
             int t = tid;
-            asm volatile("" : "+v"(t));      // formed here, not earlier
-            pass_twiddles<T, B, S>(wp, tw, t);
+            asm volatile("" : "+v"(t));      // loaded here, not earlier
+            pass_twiddles<T, B, S>(w, tw, t);
         } else {
             int k = tid & (p - 1);
             asm volatile("" : "+v"(k));      // read here, not hoisted out of the caller's loops
-#pragma unroll
-            for (int q = 0; q < 7; ++q) wp[q] = tl[tl_offset(B, S) + q * p + k];
+            const cx<T>* row = tl + tl_offset<T>(B, S) + k;
+            w.w1 = row[0];
+            w.w2 = row[p];
+            w.w4 = row[2 * p];
+            if constexpr (tw_loads<T>() == 4) w.w8 = row[3 * p];
+            else w.w8 = eighth(w.w1);
         }
-    }
-#pragma unroll
-    for (int u = 0; u < NB; ++u) {
-        const int i = tid + u * NT;
-        const int k = i & (p - 1);
-        cx<T> x[r];
-#pragma unroll
-        for (int q = 0; q < r; ++q) x[q] = v[u + q * NB];
-        if constexpr (!first) {
-#pragma unroll
-            for (int q = 1; q < r; ++q) {
-                cx<T> t = wp[q - 1];
-                if constexpr (SIGN < 0) t.im = -t.im;
-                x[q] = cmul(x[q], t);
-            }
-        }
-        dft<SIGN, r>(x);
+        dft8_tw<SIGN>(v, w);
         if constexpr (!last) {
-            const int base = (i - k) * r + k;
+            const int k = tid & (p - 1);
+            const int base = (tid - k) * 8 + k;
 #pragma unroll
-            for (int q = 0; q < r; ++q) out[lds_slot<T>(base + q * p)] = x[q];
-        } else {
-#pragma unroll
-            for (int q = 0; q < r; ++q) v[u + q * NB] = x[q];
+            for (int q = 0; q < 8; ++q) out[lds_slot<T>(base + q * p)] = v[q];
         }
     }
-    if constexpr (!last) passes_warm<T, B, R, SIGN, S + 1, NP, DBUF, TWS>(v, buf0, buf1, wall, tw, tl, tid);
+    if constexpr (!last) passes<T, B, SIGN, S + 1, NP, DBUF, TWS>(v, buf0, buf1, wall, tw, tl, tid);
 }
 
-// B-point transform as block_fft (DBUF = false: buf1 unused) or block_fft_db
-// (DBUF: buf0 and buf1 swapped on return when the exchange count is odd),
-// with the twiddles from the source TWS (above; `tl` for TW_TABLE).
-template <typename T, int B, int R, int SIGN, bool DBUF, int TWS>
-__device__ __forceinline__ void block_fft_warm(cx<T> (&v)[R], cx<T>*& buf0, cx<T>*& buf1,
-                                               const cx<T>* __restrict__ tw, int tid, const cx<T>* tl = nullptr) {
-    static_assert((B & (B - 1)) == 0 && B >= 64 && R == 8, "power-of-two block, 8 points per thread");
+// B-point transform of the workgroup's registers (see the file comment); must
+// be called by every thread of the workgroup (it contains barriers).
+//   DBUF = false: one exchange buffer of B elements (buf1 unused), two
+//     barriers per exchange.
+//   DBUF = true: passes alternate between two buffers: pass s writes
+//     buf[s % 2] and pass s + 1 reads it after one barrier; the barrier after
+//     the reads is not needed, since the next write goes to the other buffer,
+//     whose last readers passed the barrier before this read.  A call ends
+//     having read buf[(E - 1) % 2] (E exchanges); the next call must start by
+//     writing the other buffer, so for odd E the two pointers are swapped on
+//     return.  LDS accesses made otherwise to either buffer must be separated
+//     from the call by a barrier.
+// `tw` holds exp(+2 pi i j / B), j = 0..B-1; `regs` for TW_REGS, `tl` for
+// TW_TABLE.
+template <typename T, int B, int SIGN, bool DBUF, int TWS>
+__device__ __forceinline__ void block_fft(cx<T> (&v)[8], cx<T>*& buf0, cx<T>*& buf1, const cx<T>* __restrict__ tw,
+                                          int tid, const Twiddles<T, B>* regs = nullptr, const cx<T>* tl = nullptr) {
+    static_assert((B & (B - 1)) == 0 && B >= 64, "power-of-two block of at least 64 points");
     constexpr int NP = n_passes(B);
-    static_assert(NP >= 2, "at least two passes");
-    cx<T> w[NP - 1][7];
-    if constexpr (TWS == TW_AHEAD) {
-        int t = tid;
-        asm volatile("" : "+v"(t));      // formed inside this call
-        all_twiddles<T, B, 1, NP>(w, tw, t);
+    if constexpr (TWS == TW_TABLE_LEAN) asm volatile("" : "+v"(tid));
+    PassTw<T> w[NP - 1];
+    if constexpr (TWS == TW_REGS) {
+#pragma unroll
+        for (int i = 0; i < NP - 1; ++i) w[i] = regs->w[i];
     }
-    passes_warm<T, B, R, SIGN, 0, NP, DBUF, TWS>(v, buf0, buf1, w, tw, tl, tid);
+    passes<T, B, SIGN, 0, NP, DBUF, TWS>(v, buf0, buf1, w, tw, tl, tid);
     if constexpr (DBUF && (NP - 1) % 2 == 1) {
         cx<T>* s = buf0;
         buf0 = buf1;
         buf1 = s;
     }
-}
-
-// B-point transform of the workgroup's registers (see the file comment).
-// `tw` holds exp(+2 pi i j / B), j = 0..B-1.  Must be called by every
-// thread of the workgroup (it contains barriers).  COLD: the twiddle index
-// is hidden from the optimiser, so the twiddles are loaded inside each pass
-// instead of being kept in registers across the caller's code; for
-// transforms outside the hot loop, whose twiddles would otherwise hold
-// registers for the whole kernel.
-template <typename T, int B, int R, int SIGN, bool COLD = false>
-__device__ __forceinline__ void block_fft(cx<T> (&v)[R], cx<T>* lds,
-                                          const cx<T>* __restrict__ tw, int tid) {
-    static_assert((B & (B - 1)) == 0 && B >= 64, "power-of-two block");
-    fft_from<T, B, R, SIGN, 1, COLD>(v, lds, tw, tid);
 }
 
 }  // namespace mpa

@@ -57,7 +57,24 @@ struct StepTables {
     const double* __restrict__ taper;          // B window weights
 };
 
-// One field: one workgroup per block.
+// The LDS twiddle table of an FP64 plan's transforms, filled at the start of
+// the kernel (28 KB at B = 4096, beside 128 KB of exchange buffers); FP32
+// plans have none.
+#define LDS_TWIDDLES(T, B)                                                             \
+    __shared__ cx<double> twl[sizeof(T) == 8 ? tl_elems<double>(B) : 1];               \
+    if constexpr (sizeof(T) == 8) {                                                    \
+        fill_twiddle_table<double, B>(twl, tw64, threadIdx.x, B / PTS);                \
+        __syncthreads();                                                               \
+    }
+
+// One field: one workgroup per block.  Bound by the instructions of its 19
+// dependent transforms (M = 4, two sweeps) and the exchange latency that two
+// waves per SIMD leave open.  2^22 modes, 2048 blocks of 4096, 8 long steps:
+// 2.62 ms with 8-point DFTs behind seven twiddle products and the last node
+// selected per element, 2.29 ms with the passes of block_fft.hpp, the last
+// node behind a uniform branch and the node's two scales folded (1446 against
+// 1681 vector instructions per node); 2^18 modes in FP64 (NIT = 2): 84 against
+// 60 us per step with double-buffered transforms and an LDS twiddle table.
 // Both kernels are held to 256 registers per lane (two waves per SIMD): at
 // B <= 2048 a workgroup has at most one wave per SIMD, and the compiler would
 // otherwise take up to 512 and keep one workgroup per CU.
@@ -68,8 +85,9 @@ mpa_block_kernel(const cx<T>* __restrict__ in, cx<T>* __restrict__ out, long lon
                  const T* __restrict__ node_scale, const cx<T>* __restrict__ tw,
                  const cx<double>* __restrict__ tw64, const double* __restrict__ taper, int M, T sigma,
                  double out_scale) {
-    // two FP64 exchange buffers (the node transforms use the first)
-    __shared__ cx<double> lds64[2 * lds_elems<B>()];
+    // two FP64 exchange buffers (FP32 node transforms use the first)
+    __shared__ cx<double> lds64[2 * B];
+    LDS_TWIDDLES(T, B)
     const long long c0 = (long long)blockIdx.x * core;
     const int thread = threadIdx.x;
 #include "long_step_body.inc"
@@ -87,7 +105,8 @@ mpa_batch_kernel(const cx<T>* __restrict__ fin, cx<T>* __restrict__ fout,
                  const T* __restrict__ node_scale, const cx<T>* __restrict__ tw,
                  const cx<double>* __restrict__ tw64, const double* __restrict__ taper, int M,
                  double sigma_span, double out_scale) {
-    __shared__ cx<double> lds64[2 * lds_elems<B>()];
+    __shared__ cx<double> lds64[2 * B];
+    LDS_TWIDDLES(T, B)
     for (int w = blockIdx.x; w < n_items; w += gridDim.x) {
         const int2 it = items[w];
         const cx<T>* __restrict__ in = fin + offset[it.x];

@@ -54,7 +54,7 @@ np_init_kernel(const cx<T>* __restrict__ in, cx<double>* __restrict__ psi0_buf, 
                const cx<double>* __restrict__ tw64, const double* __restrict__ taper, T sigma) {
     constexpr int R = PTS;
     constexpr int NT = B / R;
-    __shared__ cx<double> lds64[lds_elems<B>()];
+    __shared__ cx<double> lds64[B];
     cx<T>* ldsT = reinterpret_cast<cx<T>*>(lds64);
     const int tid = threadIdx.x;
     const long long c0 = (long long)blockIdx.x * core;
@@ -70,8 +70,10 @@ np_init_kernel(const cx<T>* __restrict__ in, cx<double>* __restrict__ psi0_buf, 
     }
     cx<double>* e0 = lds64;
     cx<double>* e1 = lds64;
-    block_fft_warm<double, B, R, +1, false, TW_AHEAD>(psi0, e0, e1, tw64, tid);   // as the fused kernel
-    block_fft<T, B, R, +1>(cur, ldsT, tw, tid);
+    block_fft<double, B, +1, false, TW_AHEAD>(psi0, e0, e1, tw64, tid);   // as the fused kernel
+    cx<T>* l0 = ldsT;
+    cx<T>* l1 = ldsT;
+    block_fft<T, B, +1, false, TW_AHEAD>(cur, l0, l1, tw, tid);
     const T d0 = sigma * node_scale[1];
     const size_t base = (size_t)blockIdx.x * B;
 #pragma unroll
@@ -95,10 +97,9 @@ np_node_kernel(const cx<double>* __restrict__ psi0_buf, const cx<T>* __restrict_
     const int l = k % M + 1;
     const int b = (k / M) * XCDS + xcd;
     if (b >= n_blocks) return;                    // the whole workgroup leaves together
-    __shared__ cx<T> lds[lds_elems<B>()];
-    // the transforms' twiddles from an LDS table (the B-point table's values, the
-    // arithmetic of block_fft), filled while the trapezoid sums load
-    __shared__ cx<T> twl[tl_elems(B)];
+    __shared__ cx<T> lds[B];
+    // the transforms' twiddles from an LDS table, filled while the trapezoid sums load
+    __shared__ cx<T> twl[tl_elems<T>(B)];
     fill_twiddle_table<T, B>(twl, tw, threadIdx.x, B / PTS);
     const int tid = threadIdx.x;
     const size_t base = (size_t)b * B;
@@ -130,25 +131,21 @@ np_node_kernel(const cx<double>* __restrict__ psi0_buf, const cx<T>* __restrict_
     }
 #pragma unroll
     for (int m = 0; m < R; ++m) ph[m] = phase[(size_t)l * B + tid + NT * m];
-    const T cl = node_scale[2 * l];
-    const T dl = sigma * node_scale[2 * l + 1];
+    const T c3 = cube_scale<T>(node_scale[2 * l], sigma * node_scale[2 * l + 1]);
     // steps 2-3: A = e^{Gamma_l} F^-1[psi e^{i beta_l}]
 #pragma unroll
     for (int m = 0; m < R; ++m) cur[m] = cmul(cur[m], ph[m]);
     cx<T>* l0 = lds;
     cx<T>* l1 = lds;
     __syncthreads();                              // the twiddle table is complete
-    block_fft_warm<T, B, R, -1, false, TW_TABLE>(cur, l0, l1, tw, tid, twl);
+    block_fft<T, B, -1, false, TW_TABLE>(cur, l0, l1, tw, tid, nullptr, twl);
 #pragma unroll
-    for (int m = 0; m < R; ++m) {
-        const cx<T> a = scale(cur[m], cl);
-        cur[m] = scale(a, norm2(a));
-    }
+    for (int m = 0; m < R; ++m) cur[m] = cube(cur[m], c3);
     // step 4: U_l = i sigma dz e^{-Gamma_l} e^{-i beta_l} F[|A|^2 A]
-    block_fft_warm<T, B, R, +1, false, TW_TABLE>(cur, l0, l1, tw, tid, twl);
+    block_fft<T, B, +1, false, TW_TABLE>(cur, l0, l1, tw, tid, nullptr, twl);
 #pragma unroll
     for (int m = 0; m < R; ++m)
-        u_cur[(row + l - 1) * B + tid + NT * m] = rot<+1>(scale(cmulc(cur[m], ph[m]), dl));
+        u_cur[(row + l - 1) * B + tid + NT * m] = rot<+1>(cmulc(cur[m], ph[m]));
 }
 
 template <typename T, int B>
@@ -159,7 +156,7 @@ np_final_kernel(const cx<double>* __restrict__ psi0_buf, const cx<T>* __restrict
                 double out_scale) {
     constexpr int R = PTS;
     constexpr int NT = B / R;
-    __shared__ cx<double> lds64[lds_elems<B>()];
+    __shared__ cx<double> lds64[B];
     const int tid = threadIdx.x;
     const int b = blockIdx.x;
     const size_t base = (size_t)b * B;
@@ -187,7 +184,7 @@ np_final_kernel(const cx<double>* __restrict__ psi0_buf, const cx<T>* __restrict
     }
     cx<double>* e0 = lds64;
     cx<double>* e1 = lds64;
-    block_fft_warm<double, B, R, -1, false, TW_AHEAD>(v, e0, e1, tw64, tid);      // as the fused kernel
+    block_fft<double, B, -1, false, TW_AHEAD>(v, e0, e1, tw64, tid);      // as the fused kernel
     const long long c0 = (long long)b * core;
     const long long rest = n - c0;
     const int clen = rest < core ? (int)rest : core;

@@ -29,8 +29,10 @@ ss_run_small_kernel(cx<ST>* __restrict__ field, const cx<double>* __restrict__ h
                     const cx<double>* __restrict__ full_ph, const cx<double>* __restrict__ tw, int steps,
                     double sdz, double half_scale, double full_scale, double end_scale) {
     constexpr int R = SS_PTS, NT = B / R;
-    __shared__ cx<double> lds[lds_elems<B>()];
+    __shared__ cx<double> lds[B];
     const int tid = threadIdx.x;
+    cx<double>* l0 = lds;
+    cx<double>* l1 = lds;
     cx<double> v[R], hp[R], fp[R];
 #pragma unroll
     for (int m = 0; m < R; ++m) {
@@ -41,14 +43,14 @@ ss_run_small_kernel(cx<ST>* __restrict__ field, const cx<double>* __restrict__ h
         fp[m] = full_ph[k];
     }
     // L dz/2
-    block_fft<double, B, R, +1>(v, lds, tw, tid);
+    block_fft<double, B, +1, false, TW_PASS>(v, l0, l1, tw, tid);
 #pragma unroll
     for (int m = 0; m < R; ++m) v[m] = scale(cmul(v[m], hp[m]), half_scale);
-    block_fft<double, B, R, -1>(v, lds, tw, tid);
+    block_fft<double, B, -1, false, TW_PASS>(v, l0, l1, tw, tid);
     for (int j = 1; j <= steps; ++j) {
 #pragma unroll
         for (int m = 0; m < R; ++m) v[m] = kick(v[m], sdz);
-        block_fft<double, B, R, +1>(v, lds, tw, tid);
+        block_fft<double, B, +1, false, TW_PASS>(v, l0, l1, tw, tid);
         if (j < steps) {
 #pragma unroll
             for (int m = 0; m < R; ++m) v[m] = scale(cmul(v[m], fp[m]), full_scale);
@@ -56,7 +58,7 @@ ss_run_small_kernel(cx<ST>* __restrict__ field, const cx<double>* __restrict__ h
 #pragma unroll
             for (int m = 0; m < R; ++m) v[m] = scale(cmul(v[m], hp[m]), end_scale);
         }
-        block_fft<double, B, R, -1>(v, lds, tw, tid);
+        block_fft<double, B, -1, false, TW_PASS>(v, l0, l1, tw, tid);
     }
 #pragma unroll
     for (int m = 0; m < R; ++m) field[tid + NT * m] = cx<ST>{ST(v[m].re), ST(v[m].im)};

@@ -13,9 +13,7 @@
 // The field is stored in ST (float or double) between the passes; the
 // arithmetic, the twiddles (including the N-point twiddle w_N^{n2 k1},
 // formed in FP64 from two sqrt(N)-point tables), the phase tables and the
-// scales are FP64 for both storage types (the transforms form six of each
-// pass's seven twiddles by FP64 products from one table load, see
-// block_fft_warm).  Rounding a constant to FP32 would
+// scales are FP64 for both storage types.  Rounding a constant to FP32 would
 // bias every step alike, so that the error would grow linearly with the
 // number of steps; rounding the evolving field when it is stored does not.
 //
@@ -71,7 +69,7 @@ ss_rows_kernel(cx<ST>* __restrict__ y, int n1, const cx<double>* __restrict__ tw
                const cx<double>* __restrict__ twl, const cx<double>* __restrict__ twh, int split,
                const cx<double>* __restrict__ phase, double scl) {
     constexpr int R = SL_PTS, NT = N2 / R;
-    __shared__ cx<double> lds[TR * lds_elems<N2>()];
+    __shared__ cx<double> lds[TR * N2];
     const int r = threadIdx.x / NT, t = threadIdx.x - r * NT;
     const int k1 = blockIdx.x * TR + r;
     cx<ST>* row = y + (size_t)k1 * N2;
@@ -79,12 +77,12 @@ ss_rows_kernel(cx<ST>* __restrict__ y, int n1, const cx<double>* __restrict__ tw
     cx<double> v[R];
 #pragma unroll
     for (int m = 0; m < R; ++m) v[m] = load_w(row[t + NT * m]);
-    cx<double>* b0 = lds + r * lds_elems<N2>();
+    cx<double>* b0 = lds + r * N2;
     cx<double>* b1 = b0;
-    block_fft_warm<double, N2, R, +1, false, TW_AHEAD>(v, b0, b1, tw2, t);
+    block_fft<double, N2, +1, false, TW_AHEAD>(v, b0, b1, tw2, t);
 #pragma unroll
     for (int m = 0; m < R; ++m) v[m] = scale(cmul(v[m], prow[t + NT * m]), scl);
-    block_fft_warm<double, N2, R, -1, false, TW_AHEAD>(v, b0, b1, tw2, t);
+    block_fft<double, N2, -1, false, TW_AHEAD>(v, b0, b1, tw2, t);
     // w_N^{n2 k1} for n2 = t + NT m: w_N^{t k1} (w_N^{NT k1})^m, two table
     // lookups per thread instead of one per point
     cx<double> w = big_twiddle(twl, twh, split, t * k1);
@@ -103,26 +101,26 @@ __global__ void __launch_bounds__(TC * N1 / SL_PTS) __attribute__((amdgpu_waves_
 ss_cols_kernel(cx<ST>* __restrict__ y, int n2, const cx<double>* __restrict__ tw1,
                const cx<double>* __restrict__ twl, const cx<double>* __restrict__ twh, int split, double sdz) {
     constexpr int R = SL_PTS, NT = N1 / R;
-    __shared__ cx<double> lds[TC * lds_elems<N1>()];
+    __shared__ cx<double> lds[TC * (N1 + N1 / 8)];
     // column group of this workgroup: contiguous runs of groups per XCD
     const int groups = gridDim.x, b = blockIdx.x;
     const int grp = (groups % 8 == 0) ? (b % 8) * (groups / 8) + b / 8 : b;
     const int c = threadIdx.x % TC, t = threadIdx.x / TC;
     const int col = grp * TC + c;
-    cx<double>* my = lds + c * lds_elems<N1>();
+    cx<double>* my = lds + c * (N1 + N1 / 8);
     cx<double>* my1 = my;
     cx<double> v[R];
 #pragma unroll
     for (int m = 0; m < R; ++m) v[m] = load_w(y[(size_t)(t + NT * m) * n2 + col]);
     if constexpr (MODE != SS_COL_FIRST) {
-        block_fft_warm<double, N1, R, -1, false, TW_AHEAD>(v, my, my1, tw1, t);   // x[N2 n1 + n2], n1 = t + NT m
+        block_fft<double, N1, -1, false, TW_AHEAD>(v, my, my1, tw1, t);   // x[N2 n1 + n2], n1 = t + NT m
     }
     if constexpr (MODE == SS_COL_MID) {
 #pragma unroll
         for (int m = 0; m < R; ++m) v[m] = kick_sl(v[m], sdz);
     }
     if constexpr (MODE != SS_COL_LAST) {
-        block_fft_warm<double, N1, R, +1, false, TW_AHEAD>(v, my, my1, tw1, t);   // Y[k1][n2], k1 = t + NT m
+        block_fft<double, N1, +1, false, TW_AHEAD>(v, my, my1, tw1, t);   // Y[k1][n2], k1 = t + NT m
         // w_N^{col k1} for k1 = t + NT m, as in the row kernel
         cx<double> w = big_twiddle(twl, twh, split, col * t);
         const cx<double> step = big_twiddle(twl, twh, split, col * NT);

@@ -72,13 +72,14 @@ win_cols_kernel(const cx<TIN>* __restrict__ src, cx<TOUT>* __restrict__ dst, int
                 const cx<TK>* __restrict__ tw1, const cx<TK>* __restrict__ twl,
                 const cx<TK>* __restrict__ twh, int split, TK cnode) {
     constexpr int R = WP, NT = N1 / R;
-    __shared__ cx<TK> lds[TC * lds_elems<N1>()];
+    __shared__ cx<TK> lds[TC * (N1 + N1 / 8)];
     const int c = threadIdx.x % TC, t = threadIdx.x / TC;
     const int col = blockIdx.x * TC + c;
     const size_t woff = (size_t)blockIdx.y * N1 * n2;      // window of a blocked plan
     src += woff;
     dst += woff;
-    cx<TK>* my = lds + c * lds_elems<N1>();
+    cx<TK>* my = lds + c * (N1 + N1 / 8);
+    cx<TK>* my1 = my;
     cx<TK> v[R];
 #pragma unroll
     for (int m = 0; m < R; ++m) {
@@ -90,7 +91,7 @@ win_cols_kernel(const cx<TIN>* __restrict__ src, cx<TOUT>* __restrict__ dst, int
             v[m] = cx<TK>{TK(x.re), TK(x.im)};
         }
     }
-    if constexpr (MODE == WC_NODE || MODE == WC_INV) block_fft<TK, N1, R, -1>(v, my, tw1, t);
+    if constexpr (MODE == WC_NODE || MODE == WC_INV) block_fft<TK, N1, -1, false, TW_AHEAD>(v, my, my1, tw1, t);
     if constexpr (MODE == WC_NODE) {
 #pragma unroll
         for (int m = 0; m < R; ++m) {
@@ -99,7 +100,7 @@ win_cols_kernel(const cx<TIN>* __restrict__ src, cx<TOUT>* __restrict__ dst, int
         }
     }
     if constexpr (MODE != WC_INV) {
-        block_fft<TK, N1, R, +1>(v, my, tw1, t);
+        block_fft<TK, N1, +1, false, TW_AHEAD>(v, my, my1, tw1, t);
 #pragma unroll
         for (int m = 0; m < R; ++m) {
             const int k1 = t + NT * m;
@@ -138,12 +139,13 @@ win_rows_kernel(WinRowArgs a, const cx<T>* __restrict__ tw2, const cx<double>* _
                 long long N, long long Ntot) {
     using TP = typename std::conditional<MODE == WR_PSI0 || MODE == WR_FINAL, double, T>::type;
     constexpr int R = WP, NT = N2 / R;
-    __shared__ cx<TP> lds[TR * lds_elems<N2>()];
+    __shared__ cx<TP> lds[TR * N2];
     const int r = threadIdx.x / NT, t = threadIdx.x - r * NT;
     const long long k1 = (long long)blockIdx.x * TR + r;
     const size_t base = (size_t)k1 * N2;
     const size_t woff = (size_t)blockIdx.y * N;            // window of a blocked plan (tables: no offset)
-    cx<TP>* my = lds + r * lds_elems<N2>();
+    cx<TP>* my = lds + r * N2;
+    cx<TP>* my1 = my;
     const cx<TP>* __restrict__ tw = nullptr;
     if constexpr (sizeof(TP) == 8) tw = reinterpret_cast<const cx<TP>*>(tw2_64);
     else tw = reinterpret_cast<const cx<TP>*>(tw2);
@@ -153,7 +155,7 @@ win_rows_kernel(WinRowArgs a, const cx<T>* __restrict__ tw2, const cx<double>* _
         const cx<TP>* src = static_cast<const cx<TP>*>(a.src) + woff;
 #pragma unroll
         for (int m = 0; m < R; ++m) v[m] = src[base + t + NT * m];
-        block_fft<TP, N2, R, +1>(v, my, tw, t);
+        block_fft<TP, N2, +1, false, TW_AHEAD>(v, my, my1, tw, t);
     }
     if constexpr (MODE == WR_PSI0) {
 #pragma unroll
@@ -196,7 +198,7 @@ win_rows_kernel(WinRowArgs a, const cx<T>* __restrict__ tw2, const cx<double>* _
                 v[m] = scale(cmul(psi0[i], static_cast<const cx<double>*>(a.ph_last)[i]), a.out_scale);
             }
         }
-        block_fft<TP, N2, R, -1>(v, my, tw, t);
+        block_fft<TP, N2, -1, false, TW_AHEAD>(v, my, my1, tw, t);
         cx<TP>* dst = static_cast<cx<TP>*>(a.dst) + woff;
 #pragma unroll
         for (int m = 0; m < R; ++m) {
