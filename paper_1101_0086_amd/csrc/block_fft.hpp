@@ -58,6 +58,26 @@ __device__ __forceinline__ int lds_slot(int j) {
     }
 }
 
+// The slot is linear over exclusive or and changes only the low bits of j, so
+// for elements a | c with a of the thread and c known at compile time (no
+// common bits) it is (slot(a) ^ low bits of slot(c)) + the rest of c: at most
+// one operation per access, the rest in the access's offset.  `a`: slot(a) in
+// bytes.
+template <typename T>
+__device__ __forceinline__ cx<T>& lds_at(cx<T>* buf, int a, int c) {
+    constexpr int low = sizeof(T) == 4 ? 15 : 7;
+    const int s = lds_slot<T>(c);
+    return *reinterpret_cast<cx<T>*>(reinterpret_cast<char*>(buf) + (a ^ ((s & low) * (int)sizeof(cx<T>))) +
+                                     (s & ~low) * (int)sizeof(cx<T>));
+}
+
+template <typename T, bool LEAN>
+__device__ __forceinline__ int lds_base(int j) {
+    int a = lds_slot<T>(j) * (int)sizeof(cx<T>);
+    if constexpr (LEAN) asm volatile("" : "+v"(a));
+    return a;
+}
+
 // ---- small DFTs in registers (output in natural order, in place) ----------
 
 template <int SIGN, typename T>
@@ -177,10 +197,7 @@ constexpr int pass_span(int B, int s) { return s == 0 ? 1 : first_radix(B) * (1 
 //   TW_PASS   loads at the start of each pass (fewer registers)
 //   TW_TABLE  a table in LDS (fill_twiddle_table), read at the start of each
 //             pass: transforms inside a loop whose registers cannot hold them
-//   TW_TABLE_LEAN  the same, the LDS addresses formed in each call (about 90
-//             integer operations at 4096 points) instead of being kept across
-//             the caller's loop: callers that spill otherwise
-enum TwiddleSource { TW_REGS = 0, TW_AHEAD = 1, TW_PASS = 2, TW_TABLE = 3, TW_TABLE_LEAN = 4 };
+enum TwiddleSource { TW_REGS = 0, TW_AHEAD = 1, TW_PASS = 2, TW_TABLE = 3 };
 
 // e^{i pi/4} w: from the table in FP32, formed from w in FP64 (three 16-byte
 // loads per pass instead of four, and an LDS table that fits beside two
@@ -254,7 +271,7 @@ __device__ __forceinline__ void load_twiddles(Twiddles<T, B>& t, const cx<T>* __
     all_twiddles<T, B, 1, n_passes(B)>(t.w, tw, tid);
 }
 
-template <typename T, int B, int SIGN, int S, int NP, bool DBUF, int TWS>
+template <typename T, int B, int SIGN, int S, int NP, bool DBUF, int TWS, bool LEAN>
 __device__ __forceinline__ void passes(cx<T> (&v)[8], cx<T>* buf0, cx<T>* buf1, PassTw<T> (&wall)[NP - 1],
                                        const cx<T>* __restrict__ tw, const cx<T>* tl, int tid) {
     if constexpr (TWS == TW_AHEAD) {
@@ -279,16 +296,17 @@ __device__ __forceinline__ void passes(cx<T> (&v)[8], cx<T>* buf0, cx<T>* buf1, 
 #pragma unroll
             for (int q = 0; q < r; ++q) x[q] = v[u + q * NB];
             dft<SIGN, r>(x);
-            const int base = (tid + u * NT) * r;
+            const int a = lds_base<T, LEAN>(tid * r);
 #pragma unroll
-            for (int q = 0; q < r; ++q) out[lds_slot<T>(base + q)] = x[q];
+            for (int q = 0; q < r; ++q) lds_at<T>(out, a, u * NT * r + q) = x[q];
         }
     } else {
         __syncthreads();        // the previous pass's writes are visible
+        const int ar = lds_base<T, LEAN>(tid);
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
             constexpr int order[8] = {0, 4, 2, 6, 1, 5, 3, 7};   // the order the butterflies take them in
-            v[order[q]] = in[lds_slot<T>(tid + NT * order[q])];
+            v[order[q]] = lds_at<T>(in, ar, NT * order[q]);
         }
         if constexpr (!DBUF) __syncthreads();   // every read done before this pass overwrites
         PassTw<T> w;
@@ -311,12 +329,12 @@ __device__ __forceinline__ void passes(cx<T> (&v)[8], cx<T>* buf0, cx<T>* buf1, 
         dft8_tw<SIGN>(v, w);
         if constexpr (!last) {
             const int k = tid & (p - 1);
-            const int base = (tid - k) * 8 + k;
+            const int a = lds_base<T, LEAN>((tid - k) * 8 + k);
 #pragma unroll
-            for (int q = 0; q < 8; ++q) out[lds_slot<T>(base + q * p)] = v[q];
+            for (int q = 0; q < 8; ++q) lds_at<T>(out, a, q * p) = v[q];
         }
     }
-    if constexpr (!last) passes<T, B, SIGN, S + 1, NP, DBUF, TWS>(v, buf0, buf1, wall, tw, tl, tid);
+    if constexpr (!last) passes<T, B, SIGN, S + 1, NP, DBUF, TWS, LEAN>(v, buf0, buf1, wall, tw, tl, tid);
 }
 
 // B-point transform of the workgroup's registers (see the file comment); must
@@ -332,19 +350,19 @@ __device__ __forceinline__ void passes(cx<T> (&v)[8], cx<T>* buf0, cx<T>* buf1, 
 //     return.  LDS accesses made otherwise to either buffer must be separated
 //     from the call by a barrier.
 // `tw` holds exp(+2 pi i j / B), j = 0..B-1; `regs` for TW_REGS, `tl` for
-// TW_TABLE.
-template <typename T, int B, int SIGN, bool DBUF, int TWS>
+// TW_TABLE.  LEAN: every access forms its LDS address (one operation) instead of
+// the caller's loop keeping it in a register, for callers that spill otherwise.
+template <typename T, int B, int SIGN, bool DBUF, int TWS, bool LEAN = false>
 __device__ __forceinline__ void block_fft(cx<T> (&v)[8], cx<T>*& buf0, cx<T>*& buf1, const cx<T>* __restrict__ tw,
                                           int tid, const Twiddles<T, B>* regs = nullptr, const cx<T>* tl = nullptr) {
     static_assert((B & (B - 1)) == 0 && B >= 64, "power-of-two block of at least 64 points");
     constexpr int NP = n_passes(B);
-    if constexpr (TWS == TW_TABLE_LEAN) asm volatile("" : "+v"(tid));
     PassTw<T> w[NP - 1];
     if constexpr (TWS == TW_REGS) {
 #pragma unroll
         for (int i = 0; i < NP - 1; ++i) w[i] = regs->w[i];
     }
-    passes<T, B, SIGN, 0, NP, DBUF, TWS>(v, buf0, buf1, w, tw, tl, tid);
+    passes<T, B, SIGN, 0, NP, DBUF, TWS, LEAN>(v, buf0, buf1, w, tw, tl, tid);
     if constexpr (DBUF && (NP - 1) % 2 == 1) {
         cx<T>* s = buf0;
         buf0 = buf1;
