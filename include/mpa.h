@@ -92,11 +92,15 @@ typedef enum {
  *   MPA_WAVEFRONT: one fused kernel per long step, one workgroup per block;
  *     nodes l = 1..M in turn and, at each node, all n_iter sweeps (sweep n+1
  *     at node l needs only sweep-n values at nodes <= l), with psi_0 and
- *     one running trapezoid sum per sweep held in registers.
+ *     one running trapezoid sum per sweep held in registers.  A plan of few
+ *     blocks and many nodes, whose blocks would leave most of the chip idle,
+ *     runs the node-parallel kernels instead (the same operations and sums;
+ *     n_blocks <= 4 M, M >= 8 or for MPA_C128 4, n_blocks x M <= 1024).
  *   MPA_NODE_PARALLEL: the paper's order (steps 2-6 sweep by sweep, every
- *     node of a sweep independent): n_iter + 2 launches per long step, the
- *     node work of a sweep as n_blocks x M workgroups, psi_0 and the
- *     increments of two sweeps kept in device memory (plan-owned,
+ *     node of a sweep independent): n_iter + 2 launches per long step (and
+ *     n_iter more for long trapezoid sums), the node work of a sweep as
+ *     n_blocks x M workgroups, psi_0 and the increments of two sweeps kept in
+ *     device memory (plan-owned,
  *     n_blocks x (2 M + 1) x B complex plus n_blocks x B FP64 complex).   */
 typedef enum {
     MPA_WAVEFRONT = 0,
@@ -172,7 +176,7 @@ typedef struct {
     int32_t threads_per_block;
     int64_t table_bytes;       /* device bytes of phase/twiddle/taper tables   */
     int64_t workspace_bytes;   /* device bytes of the ping-pong field buffer, plus
-                                  the node-parallel state when scheduled so     */
+                                  the node-parallel state when it runs so       */
     int32_t shift;             /* window shift in use (MPA_SHIFT_AUTO resolved) */
 } mpa_plan_info;
 

@@ -18,11 +18,12 @@ struct BatchItems {
 };
 
 // Device state of the node-parallel schedule (per block: psi_0 in FP64,
-// U_0 / 2, and the increments U_1..U_M of two sweeps, node precision).
+// U_0 / 2, and the increments U_1..U_M of two sweeps, or of one sweep and the
+// spectra psi_1..psi_M of the next, node precision).
 struct NodeBuffers {
     void* psi0;     // n_blocks x B FP64 complex
     void* half_u0;  // n_blocks x B complex
-    void* u[2];     // n_blocks x M x B complex each (sweeps alternate)
+    void* u[2];     // n_blocks x M x B complex each
 };
 
 // One fused long step over every block of one field (batch == nullptr) or

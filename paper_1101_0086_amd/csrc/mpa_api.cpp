@@ -431,7 +431,25 @@ int mpa_plan_validate(const mpa_params* params, const mpa_map* map) {
     return validate_params(params, map, &s);
 }
 
-int mpa_plan_create(const mpa_params* params, const mpa_map* map, int device, mpa_plan** out) {
+}  // extern "C"
+
+// Whether a wavefront plan's long steps run on the node-parallel kernels: the
+// fused kernel puts a block's n_iter M node evaluations one after another on
+// one CU, so with few blocks most of the chip is idle; the node-parallel
+// launches cost about as much as the evaluations of three nodes a sweep.
+// Measured per long step, fused against node-parallel, 4096-point blocks: FP64,
+// M = 4, two sweeps, 1 block 57 / 32 us, 16 blocks 58 / 34, 128 blocks 60 / 78;
+// M = 2, 1 block 34 / 30; M = 16, three sweeps, 1 block 302 / 52, 32 blocks
+// 306 / 121; FP32, M = 8, two sweeps, 1 block 61 / 34, 16 blocks 62 / 37, 128
+// blocks 62 / 80.  1024 node workgroups bound the state to 128 MiB.
+static bool nodes_fill_better(const mpa_params* prm, int n_blocks, bool window) {
+    const int64_t M = prm->M;
+    return prm->schedule == MPA_WAVEFRONT && !window && M >= (prm->precision == MPA_C64 ? 8 : 4) &&
+           n_blocks <= 4 * M && n_blocks * M <= 1024;
+}
+
+// batch: tables of a batch plan (no node-parallel state)
+static int create_plan(const mpa_params* params, const mpa_map* map, int device, bool batch, mpa_plan** out) {
     if (!out) return fail(MPA_EINVAL, "out is NULL");
     *out = nullptr;
     Schedule sched;
@@ -660,19 +678,35 @@ int mpa_plan_create(const mpa_params* params, const mpa_map* map, int device, mp
         }
         p->node_bytes = (int64_t)(NW * N * (16 * (2 + params->n_iter) + 2 * p->elem));
     }
-    if (params->schedule == MPA_NODE_PARALLEL) {
+    const bool routed = !batch && nodes_fill_better(params, p->n_blocks, p->window);
+    if (params->schedule == MPA_NODE_PARALLEL || routed) {
         const size_t nb = (size_t)p->n_blocks;
         const size_t u_bytes = nb * M * B * p->elem;
-        p->node_bytes = (int64_t)(nb * B * 16 + nb * B * p->elem + 2 * u_bytes);
-        if (hipMalloc(&p->nodes.psi0, nb * B * 16) != hipSuccess ||
-            hipMalloc(&p->nodes.half_u0, nb * B * p->elem) != hipSuccess ||
-            hipMalloc(&p->nodes.u[0], u_bytes) != hipSuccess || hipMalloc(&p->nodes.u[1], u_bytes) != hipSuccess) {
+        const int64_t bytes = (int64_t)(nb * B * 16 + nb * B * p->elem + 2 * u_bytes);
+        if (hipMalloc(&p->nodes.psi0, nb * B * 16) == hipSuccess &&
+            hipMalloc(&p->nodes.half_u0, nb * B * p->elem) == hipSuccess &&
+            hipMalloc(&p->nodes.u[0], u_bytes) == hipSuccess && hipMalloc(&p->nodes.u[1], u_bytes) == hipSuccess) {
+            p->node_bytes = bytes;
+        } else if (routed) {
+            // the fused kernel needs none of it
+            for (void** q : {&p->nodes.psi0, &p->nodes.half_u0, &p->nodes.u[0], &p->nodes.u[1]}) {
+                if (*q) (void)hipFree(*q);
+                *q = nullptr;
+            }
+            (void)hipGetLastError();
+        } else {
             plan_free(p);
-            return fail(MPA_ENOMEM, "node-parallel state allocation of %lld bytes failed", (long long)p->node_bytes);
+            return fail(MPA_ENOMEM, "node-parallel state allocation of %lld bytes failed", (long long)bytes);
         }
     }
     *out = p;
     return MPA_OK;
+}
+
+extern "C" {
+
+int mpa_plan_create(const mpa_params* params, const mpa_map* map, int device, mpa_plan** out) {
+    return create_plan(params, map, device, false, out);
 }
 
 int mpa_plan_destroy(mpa_plan* plan) {
@@ -1424,7 +1458,7 @@ int mpa_batch_plan_create(const mpa_params* params, const mpa_map* map, const mp
     mpa_params q = *params;
     q.n = nmax;
     auto* b = new mpa_batch_plan();
-    st = mpa_plan_create(&q, map, device, &b->base);
+    st = create_plan(&q, map, device, true, &b->base);
     if (st) {
         delete b;
         return st;
