@@ -25,6 +25,7 @@
 // sharing a cache line of a row share that XCD's L2.
 #include "block_fft.hpp"
 #include "ss.hpp"
+#include "ss_kick.hpp"
 
 namespace mpa {
 
@@ -33,23 +34,6 @@ constexpr int SL_PTS = 8;
 __device__ __forceinline__ cx<double> big_twiddle(const cx<double>* __restrict__ twl,
                                                   const cx<double>* __restrict__ twh, int split, int j) {
     return cmul(twh[j >> split], twl[j & ((1 << split) - 1)]);
-}
-
-// A exp(i phi), phi = sigma dz |A|^2.  For |phi| <= 1/64 (every step of a
-// weakly nonlinear link) sin and cos are their Taylor polynomials through
-// phi^7 and phi^8 (truncation below 2e-22 relative); larger phi takes the
-// library's sincos.
-__device__ __forceinline__ cx<double> kick_sl(cx<double> a, double sdz) {
-    const double phi = sdz * norm2(a);
-    double s, c;
-    if (fabs(phi) <= 0.015625) {
-        const double p2 = phi * phi;
-        s = phi * (1.0 - p2 / 6.0 * (1.0 - p2 / 20.0 * (1.0 - p2 / 42.0)));
-        c = 1.0 - p2 / 2.0 * (1.0 - p2 / 12.0 * (1.0 - p2 / 30.0 * (1.0 - p2 / 56.0)));
-    } else {
-        sincos(phi, &s, &c);
-    }
-    return cmul(a, cx<double>{c, s});
 }
 
 template <typename ST>
@@ -116,8 +100,7 @@ ss_cols_kernel(cx<ST>* __restrict__ y, int n2, const cx<double>* __restrict__ tw
         block_fft<double, N1, -1, false, TW_AHEAD>(v, my, my1, tw1, t);   // x[N2 n1 + n2], n1 = t + NT m
     }
     if constexpr (MODE == SS_COL_MID) {
-#pragma unroll
-        for (int m = 0; m < R; ++m) v[m] = kick_sl(v[m], sdz);
+        kick(v, sdz);
     }
     if constexpr (MODE != SS_COL_LAST) {
         block_fft<double, N1, +1, false, TW_AHEAD>(v, my, my1, tw1, t);   // Y[k1][n2], k1 = t + NT m
