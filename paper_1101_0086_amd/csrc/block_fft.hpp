@@ -24,8 +24,8 @@
 // twiddles (w, w^2, w^4, e^{i pi/4} w) where seven complex products in front
 // of an 8-point DFT take 80 and seven.
 // Rounding, 4096 points, rms relative error against long double: 1.34e-7 in
-// FP32 (1.19e-7 with products of table twiddles), 2.7e-16 in FP64 (4.0e-16
-// with the seven twiddles formed from one table load).
+// FP32 (1.19e-7 with products of table twiddles), 2.7e-16 in FP64, 2.4e-16 with
+// EXACT8 (2.3e-16; 4.0e-16 with the seven twiddles formed from one table load).
 //
 // SIGN = +1 is the transform with kernel exp(+i omega t) (the paper's F),
 // SIGN = -1 its unnormalised inverse.
@@ -200,10 +200,11 @@ constexpr int pass_span(int B, int s) { return s == 0 ? 1 : first_radix(B) * (1 
 enum TwiddleSource { TW_REGS = 0, TW_AHEAD = 1, TW_PASS = 2, TW_TABLE = 3 };
 
 // e^{i pi/4} w: from the table in FP32, formed from w in FP64 (three 16-byte
-// loads per pass instead of four, and an LDS table that fits beside two
-// 4096-point exchange buffers).
+// loads per pass instead of four, 4 % of a 2^22-mode split-step, and an LDS
+// table that fits beside two 4096-point exchange buffers), or from the table
+// there too where the caller asks for it (EXACT8).
 template <typename T>
-constexpr int tw_loads() { return sizeof(T) == 4 ? 4 : 3; }
+constexpr int tl_rows() { return sizeof(T) == 4 ? 4 : 3; }
 
 template <typename T>
 __device__ __forceinline__ cx<T> eighth(cx<T> w) {
@@ -212,7 +213,7 @@ __device__ __forceinline__ cx<T> eighth(cx<T> w) {
 }
 
 // pass S (S >= 1) of a B-point transform, from the B-point table `tw`
-template <typename T, int B, int S>
+template <typename T, int B, int S, bool EXACT8>
 __device__ __forceinline__ void pass_twiddles(PassTw<T>& w, const cx<T>* __restrict__ tw, int tid) {
     constexpr int p = pass_span(B, S);
     constexpr int stride = B / (p * 8);
@@ -220,7 +221,7 @@ __device__ __forceinline__ void pass_twiddles(PassTw<T>& w, const cx<T>* __restr
     w.w1 = tw[k * stride];
     w.w2 = tw[2 * k * stride];
     w.w4 = tw[4 * k * stride];
-    if constexpr (tw_loads<T>() == 4) w.w8 = tw[(k + p) * stride];
+    if constexpr (EXACT8) w.w8 = tw[(k + p) * stride];
     else w.w8 = eighth(w.w1);
 }
 
@@ -230,7 +231,7 @@ __device__ __forceinline__ void pass_twiddles(PassTw<T>& w, const cx<T>* __restr
 template <typename T>
 constexpr int tl_offset(int B, int s) {
     int o = 0;
-    for (int t = 1; t < s; ++t) o += tw_loads<T>() * pass_span(B, t);
+    for (int t = 1; t < s; ++t) o += tl_rows<T>() * pass_span(B, t);
     return o;
 }
 
@@ -255,7 +256,7 @@ __device__ __forceinline__ void fill_twiddle_table(cx<T>* tl, const cx<T>* __res
 template <typename T, int B, int S, int NP>
 __device__ __forceinline__ void all_twiddles(PassTw<T> (&w)[NP - 1], const cx<T>* __restrict__ tw, int tid) {
     if constexpr (S < NP) {
-        pass_twiddles<T, B, S>(w[S - 1], tw, tid);
+        pass_twiddles<T, B, S, sizeof(T) == 4>(w[S - 1], tw, tid);
         all_twiddles<T, B, S + 1, NP>(w, tw, tid);
     }
 }
@@ -271,14 +272,14 @@ __device__ __forceinline__ void load_twiddles(Twiddles<T, B>& t, const cx<T>* __
     all_twiddles<T, B, 1, n_passes(B)>(t.w, tw, tid);
 }
 
-template <typename T, int B, int SIGN, int S, int NP, bool DBUF, int TWS, bool LEAN>
+template <typename T, int B, int SIGN, int S, int NP, bool DBUF, int TWS, bool LEAN, bool EXACT8>
 __device__ __forceinline__ void passes(cx<T> (&v)[8], cx<T>* buf0, cx<T>* buf1, PassTw<T> (&wall)[NP - 1],
                                        const cx<T>* __restrict__ tw, const cx<T>* tl, int tid) {
     if constexpr (TWS == TW_AHEAD) {
         int t = tid;
         asm volatile("" : "+v"(t));          // loaded here, not earlier
-        if constexpr (S == 0) pass_twiddles<T, B, 1>(wall[0], tw, t);
-        if constexpr (S + 2 < NP) pass_twiddles<T, B, S + 2>(wall[S + 1], tw, t);
+        if constexpr (S == 0) pass_twiddles<T, B, 1, EXACT8>(wall[0], tw, t);
+        if constexpr (S + 2 < NP) pass_twiddles<T, B, S + 2, EXACT8>(wall[S + 1], tw, t);
     }
     constexpr int NT = B / 8;
     constexpr int p = pass_span(B, S);
@@ -308,14 +309,21 @@ __device__ __forceinline__ void passes(cx<T> (&v)[8], cx<T>* buf0, cx<T>* buf1, 
             constexpr int order[8] = {0, 4, 2, 6, 1, 5, 3, 7};   // the order the butterflies take them in
             v[order[q]] = lds_at<T>(in, ar, NT * order[q]);
         }
-        if constexpr (!DBUF) __syncthreads();   // every read done before this pass overwrites
+        if constexpr (!DBUF) {
+            // every read done before this pass overwrites.  The values are pinned in front
+            // of the barrier: with a branch after the transform the compiler sank the last
+            // pass's reads into it, below the barrier, where other waves already write
+#pragma unroll
+            for (int m = 0; m < 8; ++m) asm volatile("" : "+v"(v[m].re), "+v"(v[m].im));
+            __syncthreads();
+        }
         PassTw<T> w;
         if constexpr (TWS == TW_REGS || TWS == TW_AHEAD) {
             w = wall[S - 1];
         } else if constexpr (TWS == TW_PASS) {
             int t = tid;
             asm volatile("" : "+v"(t));      // loaded here, not earlier
-            pass_twiddles<T, B, S>(w, tw, t);
+            pass_twiddles<T, B, S, EXACT8>(w, tw, t);
         } else {
             int k = tid & (p - 1);
             asm volatile("" : "+v"(k));      // read here, not hoisted out of the caller's loops
@@ -323,7 +331,7 @@ __device__ __forceinline__ void passes(cx<T> (&v)[8], cx<T>* buf0, cx<T>* buf1, 
             w.w1 = row[0];
             w.w2 = row[p];
             w.w4 = row[2 * p];
-            if constexpr (tw_loads<T>() == 4) w.w8 = row[3 * p];
+            if constexpr (tl_rows<T>() == 4) w.w8 = row[3 * p];
             else w.w8 = eighth(w.w1);
         }
         dft8_tw<SIGN>(v, w);
@@ -334,7 +342,7 @@ __device__ __forceinline__ void passes(cx<T> (&v)[8], cx<T>* buf0, cx<T>* buf1, 
             for (int q = 0; q < 8; ++q) lds_at<T>(out, a, q * p) = v[q];
         }
     }
-    if constexpr (!last) passes<T, B, SIGN, S + 1, NP, DBUF, TWS, LEAN>(v, buf0, buf1, wall, tw, tl, tid);
+    if constexpr (!last) passes<T, B, SIGN, S + 1, NP, DBUF, TWS, LEAN, EXACT8>(v, buf0, buf1, wall, tw, tl, tid);
 }
 
 // B-point transform of the workgroup's registers (see the file comment); must
@@ -352,7 +360,7 @@ __device__ __forceinline__ void passes(cx<T> (&v)[8], cx<T>* buf0, cx<T>* buf1, 
 // `tw` holds exp(+2 pi i j / B), j = 0..B-1; `regs` for TW_REGS, `tl` for
 // TW_TABLE.  LEAN: every access forms its LDS address (one operation) instead of
 // the caller's loop keeping it in a register, for callers that spill otherwise.
-template <typename T, int B, int SIGN, bool DBUF, int TWS, bool LEAN = false>
+template <typename T, int B, int SIGN, bool DBUF, int TWS, bool LEAN = false, bool EXACT8 = sizeof(T) == 4>
 __device__ __forceinline__ void block_fft(cx<T> (&v)[8], cx<T>*& buf0, cx<T>*& buf1, const cx<T>* __restrict__ tw,
                                           int tid, const Twiddles<T, B>* regs = nullptr, const cx<T>* tl = nullptr) {
     static_assert((B & (B - 1)) == 0 && B >= 64, "power-of-two block of at least 64 points");
@@ -362,7 +370,7 @@ __device__ __forceinline__ void block_fft(cx<T> (&v)[8], cx<T>*& buf0, cx<T>*& b
 #pragma unroll
         for (int i = 0; i < NP - 1; ++i) w[i] = regs->w[i];
     }
-    passes<T, B, SIGN, 0, NP, DBUF, TWS, LEAN>(v, buf0, buf1, w, tw, tl, tid);
+    passes<T, B, SIGN, 0, NP, DBUF, TWS, LEAN, EXACT8>(v, buf0, buf1, w, tw, tl, tid);
     if constexpr (DBUF && (NP - 1) % 2 == 1) {
         cx<T>* s = buf0;
         buf0 = buf1;

@@ -17,18 +17,26 @@
 // Per long step, in the node order of the fused kernel (nodes l = 1..M, all
 // sweeps at each node) with the same precision split (node evaluations in T,
 // psi_0, the trapezoid sums and the reconstruction in FP64):
-//   init     columns(+) and rows(+) of A in FP64 -> psi_0; columns(+) and
-//            rows(+) of |A|^2 A in T -> U_0 / 2 into every sweep's sum S
-//   node     rows: psi^(s)_l e^{i beta_l}, inverse row pass;
-//            columns: inverse column pass, A = e^{Gamma_l} ., |A|^2 A,
-//            forward column pass;
-//            rows: forward row pass, U = i sigma dz e^{-Gamma_l} e^{-i beta_l} .,
-//            psi^(s+1)_l = psi_0 + S^(s) + U / 2, S^(s) += U
-//   final    rows(-) and columns(-) in FP64 of psi_M e^{i beta_M + Gamma_M}.
+//   init    columns(+) and rows(+) of |A|^2 A in T -> U_0 / 2; columns(+) of A
+//           in FP64, then one row pass: rows(+) -> psi_0, psi_0 e^{i beta_1},
+//           rows(-) in T
+//   (l, s)  columns: inverse column pass, A = e^{Gamma_l} ., sigma dz e^{-Gamma_l}
+//           |A|^2 A, forward column pass;
+//           rows: forward row pass, U = i sigma dz e^{-Gamma_l} e^{-i beta_l} .,
+//           psi^(s+1)_l = psi_0 + S^(s) + U / 2, S^(s) += U, and at once the
+//           next evaluation's psi e^{i beta} and inverse row pass (the last
+//           evaluation: psi_M e^{i beta_M + Gamma_M} and its inverse row pass
+//           in FP64)
+//   final   columns(-) in FP64.
 // Blocked plans add a gather (taper, FP64) before init and a stitch of the
 // cores after final.  This path measures the blocking error of the
 // time-blocked plans at full size and gives the autotuner blocks above 4096;
-// it makes 3 n_iter M + 6 passes over the windows per long step.
+// it makes 2 n_iter M + 5 passes over the windows per long step, bound by their
+// memory traffic: up to 2^20 modes the state stays in the 256 MiB last-level
+// cache, at 2^22 (FP64 psi_0 and sums, 200 MiB) it does not.  Long step, M = 4, two
+// sweeps, FP32, against row passes in and out of their own (3 n_iter M + 6), two
+// FP32 table gathers a point for w_N and column groups dealt round the XCDs:
+// 2^22 modes 1645 -> 803 us, 2^20 511 -> 241, 2^16 176 -> 104, 2^13 140 -> 93.
 #include <algorithm>
 #include <type_traits>
 
@@ -41,7 +49,6 @@ namespace {
 
 constexpr int WP = 8;          // points per thread
 constexpr int ROW_THREADS = 256;
-constexpr int COL_POINTS = 2048;
 
 template <typename T>
 __device__ __forceinline__ cx<double> widen(cx<T> a) { return {double(a.re), double(a.im)}; }
@@ -56,6 +63,38 @@ __device__ __forceinline__ cx<T> wN(const cx<T>* __restrict__ twl, const cx<T>* 
     return cmul(twh[j >> split], twl[j & ((1LL << split) - 1)]);
 }
 
+// w_N^{a (i0 + m di)}, m = 0..7, one call per m in turn: FP32 transforms take the
+// powers from two FP64 lookups and a recurrence in FP64 (rounded once each;
+// two FP32 gathers a point cost more than the transform's own loads), FP64
+// ones look every power up.
+template <typename T>
+struct Powers {
+    const cx<double>* __restrict__ twl;
+    const cx<double>* __restrict__ twh;
+    int split;
+    long long j, dj;
+    cx<double> w, step;
+    __device__ __forceinline__ Powers(const cx<double>* __restrict__ l, const cx<double>* __restrict__ h, int sp,
+                                      long long a, long long i0, long long di)
+        : twl(l), twh(h), split(sp), j(a * i0), dj(a * di) {
+        if constexpr (sizeof(T) == 4) {
+            w = wN(twl, twh, split, j);
+            step = wN(twl, twh, split, dj);
+        }
+    }
+    __device__ __forceinline__ cx<T> next() {
+        if constexpr (sizeof(T) == 4) {
+            const cx<T> r = narrow<T>(w);
+            w = cmul(w, step);
+            return r;
+        } else {
+            const cx<T> r = wN(twl, twh, split, j);
+            j += dj;
+            return r;
+        }
+    }
+};
+
 }  // namespace
 
 enum WinColMode { WC_FWD = 0, WC_FWD_CUBE = 1, WC_NODE = 2, WC_INV = 3 };
@@ -64,22 +103,31 @@ enum WinColMode { WC_FWD = 0, WC_FWD_CUBE = 1, WC_NODE = 2, WC_INV = 3 };
 // read consecutive columns of one row).  Loads TIN, computes in TK, stores TOUT.
 //   WC_FWD       forward column pass
 //   WC_FWD_CUBE  |x|^2 x in FP64, rounded to TK, then the forward column pass
-//   WC_NODE      inverse column pass, A = c A, |A|^2 A, forward column pass
+//   WC_NODE      inverse column pass, A = c a, d |A|^2 A, forward column pass
 //   WC_INV       inverse column pass
+// Column groups go to the XCDs in contiguous runs (workgroup b runs on XCD
+// b mod 8), so that the groups that share a cache line of a row share that
+// XCD's L2; the columns' exchange buffers are offset so that the lanes the LDS
+// serves together (16 of 8 bytes, 8 of 16 bytes) meet distinct banks.
 template <typename TIN, typename TK, typename TOUT, int N1, int TC, int MODE>
 __global__ void __launch_bounds__(TC * N1 / WP)
 win_cols_kernel(const cx<TIN>* __restrict__ src, cx<TOUT>* __restrict__ dst, int n2,
-                const cx<TK>* __restrict__ tw1, const cx<TK>* __restrict__ twl,
-                const cx<TK>* __restrict__ twh, int split, TK cnode) {
+                const cx<TK>* __restrict__ tw1, const cx<double>* __restrict__ twl,
+                const cx<double>* __restrict__ twh, int split, TK cnode, TK dnode) {
     constexpr int R = WP, NT = N1 / R;
-    __shared__ cx<TK> lds[TC * (N1 + N1 / 8)];
+    constexpr int group = sizeof(TK) == 4 ? 16 : 8;
+    constexpr int stride = N1 + (group > TC ? group / TC : 1);
+    constexpr bool DBUF = sizeof(TK) == 4;
+    __shared__ cx<TK> lds[(DBUF ? 2 : 1) * TC * stride];
+    const int groups = gridDim.x, b = blockIdx.x;
+    const int grp = groups % 8 == 0 ? (b % 8) * (groups / 8) + b / 8 : b;
     const int c = threadIdx.x % TC, t = threadIdx.x / TC;
-    const int col = blockIdx.x * TC + c;
+    const int col = grp * TC + c;
     const size_t woff = (size_t)blockIdx.y * N1 * n2;      // window of a blocked plan
     src += woff;
     dst += woff;
-    cx<TK>* my = lds + c * (N1 + N1 / 8);
-    cx<TK>* my1 = my;
+    cx<TK>* my = lds + c * stride;
+    cx<TK>* my1 = my + (DBUF ? TC * stride : 0);
     cx<TK> v[R];
 #pragma unroll
     for (int m = 0; m < R; ++m) {
@@ -91,123 +139,122 @@ win_cols_kernel(const cx<TIN>* __restrict__ src, cx<TOUT>* __restrict__ dst, int
             v[m] = cx<TK>{TK(x.re), TK(x.im)};
         }
     }
-    if constexpr (MODE == WC_NODE || MODE == WC_INV) block_fft<TK, N1, -1, false, TW_AHEAD>(v, my, my1, tw1, t);
+    if constexpr (MODE == WC_NODE || MODE == WC_INV) block_fft<TK, N1, -1, DBUF, TW_AHEAD, false, true>(v, my, my1, tw1, t);
     if constexpr (MODE == WC_NODE) {
 #pragma unroll
-        for (int m = 0; m < R; ++m) {
-            const cx<TK> a = scale(v[m], cnode);
-            v[m] = scale(a, norm2(a));
-        }
+        for (int m = 0; m < R; ++m) v[m] = cube(scale(v[m], cnode), dnode);
     }
     if constexpr (MODE != WC_INV) {
-        block_fft<TK, N1, +1, false, TW_AHEAD>(v, my, my1, tw1, t);
+        block_fft<TK, N1, +1, DBUF, TW_AHEAD, false, true>(v, my, my1, tw1, t);
+        Powers<TK> w(twl, twh, split, col, t, NT);
 #pragma unroll
-        for (int m = 0; m < R; ++m) {
-            const int k1 = t + NT * m;
-            v[m] = cmul(v[m], wN(twl, twh, split, (long long)col * k1));
-        }
+        for (int m = 0; m < R; ++m) v[m] = cmul(v[m], w.next());
     }
 #pragma unroll
     for (int m = 0; m < R; ++m) dst[(size_t)(t + NT * m) * n2 + col] = cx<TOUT>{TOUT(v[m].re), TOUT(v[m].im)};
 }
 
-enum WinRowMode { WR_PSI0 = 0, WR_U0 = 1, WR_NODE_IN = 2, WR_NODE_OUT = 3, WR_FINAL = 4 };
+enum WinRowMode { WR_FIRST = 0, WR_U0 = 1, WR_NODE = 2, WR_LAST = 3 };
 
 struct WinRowArgs {
-    const void* src;          // row-pass input (T, or FP64 for WR_PSI0)
-    void* dst;                // WR_NODE_IN / WR_FINAL output (T / FP64)
-    double* psi0;             // N FP64 complex (psi_0, replaced by psi_M at the last evaluation)
-    double* S;                // n_iter x N FP64 complex running sums
-    void* cur;                // N complex (T): psi^(s)_l of the next evaluation
-    const void* ph;           // node phasors (T), spectral order
+    const void* src;          // row-pass input (T, or FP64 for WR_FIRST)
+    void* dst;                // WR_FIRST / WR_NODE output (T), WR_LAST (FP64)
+    double* psi0;             // N FP64 complex
+    double* S;                // FP64 complex running sums of this sweep
+    void* u0;                 // N complex (T): U_0 / 2, every sweep's sum before node 1
+    const void* ph;           // this node's phasors (T), spectral order
+    const void* ph_next;      // the next evaluation's
     const void* ph_last;      // node-M phasors (FP64), spectral order
-    double dl, half_d0, out_scale;
-    int n_iter, s, first, last_node;
+    double half_d0, out_scale;
+    int first_node, last_node, last_sweep;
 };
 
 // TR rows of N2 points per workgroup.
-//   WR_PSI0      forward row pass (FP64) -> psi_0
-//   WR_U0        forward row pass (T) -> U_0 / 2 = i d0 / 2 . into every S^(s)
-//   WR_NODE_IN   (first ? psi_0 : cur) e^{i beta_l}, inverse row pass, w_N^{-n2 k1} -> dst (T)
-//   WR_NODE_OUT  forward row pass, U, Eq. 6 update of cur / psi_M and S^(s)
-//   WR_FINAL     psi_M e^{i beta_M} e^{Gamma_M} (FP64), inverse row pass, w_N^{-n2 k1} -> dst (FP64)
+//   WR_U0     forward row pass (T) -> U_0 / 2 = i d0 / 2 .
+//   WR_FIRST  forward row pass (FP64) -> psi_0; psi_0 e^{i beta_1}, inverse row pass,
+//             w_N^{-n2 k1} -> dst (T)
+//   WR_NODE   forward row pass, U, Eq. 6 update of S^(s); the next evaluation's
+//             psi e^{i beta}, inverse row pass, w_N^{-n2 k1} -> dst (T)
+//   WR_LAST   forward row pass, U, psi_M; psi_M e^{i beta_M} e^{Gamma_M}, inverse row
+//             pass, w_N^{-n2 k1} in FP64 -> dst
 template <typename T, int N2, int TR, int MODE>
-__global__ void __launch_bounds__(TR * N2 / WP)
+__global__ void __launch_bounds__(TR * N2 / WP) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 2)))
 win_rows_kernel(WinRowArgs a, const cx<T>* __restrict__ tw2, const cx<double>* __restrict__ tw2_64,
-                const cx<T>* __restrict__ twl, const cx<T>* __restrict__ twh,
-                const cx<double>* __restrict__ twl64, const cx<double>* __restrict__ twh64, int split,
-                long long N, long long Ntot) {
-    using TP = typename std::conditional<MODE == WR_PSI0 || MODE == WR_FINAL, double, T>::type;
+                const cx<double>* __restrict__ twl64, const cx<double>* __restrict__ twh64, int split, long long N) {
     constexpr int R = WP, NT = N2 / R;
-    __shared__ cx<TP> lds[TR * N2];
+    constexpr bool WIDE = MODE == WR_FIRST || MODE == WR_LAST || sizeof(T) == 8;   // an FP64 transform among them
+    constexpr bool DBUF = !WIDE;
+    __shared__ cx<double> lds[TR * N2];          // FP64: one buffer; FP32: two
     const int r = threadIdx.x / NT, t = threadIdx.x - r * NT;
     const long long k1 = (long long)blockIdx.x * TR + r;
-    const size_t base = (size_t)k1 * N2;
+    const size_t base = (size_t)k1 * N2 + t;
     const size_t woff = (size_t)blockIdx.y * N;            // window of a blocked plan (tables: no offset)
-    cx<TP>* my = lds + r * N2;
-    cx<TP>* my1 = my;
-    const cx<TP>* __restrict__ tw = nullptr;
-    if constexpr (sizeof(TP) == 8) tw = reinterpret_cast<const cx<TP>*>(tw2_64);
-    else tw = reinterpret_cast<const cx<TP>*>(tw2);
-    cx<double>* psi0 = reinterpret_cast<cx<double>*>(a.psi0) + woff;
-    cx<TP> v[R];
-    if constexpr (MODE == WR_PSI0 || MODE == WR_U0 || MODE == WR_NODE_OUT) {
-        const cx<TP>* src = static_cast<const cx<TP>*>(a.src) + woff;
+    cx<double>* d0 = lds + r * N2;
+    cx<double>* d1 = d0;
+    cx<T>* b0 = reinterpret_cast<cx<T>*>(d0);
+    cx<T>* b1 = b0 + (DBUF ? N2 : 0);
+    cx<double>* psi0 = reinterpret_cast<cx<double>*>(a.psi0) + woff + base;
+    cx<T> v[R];
+    cx<double> z[R];
+    if constexpr (MODE == WR_FIRST) {
+        const cx<double>* src = static_cast<const cx<double>*>(a.src) + woff + base;
 #pragma unroll
-        for (int m = 0; m < R; ++m) v[m] = src[base + t + NT * m];
-        block_fft<TP, N2, +1, false, TW_AHEAD>(v, my, my1, tw, t);
-    }
-    if constexpr (MODE == WR_PSI0) {
-#pragma unroll
-        for (int m = 0; m < R; ++m) psi0[base + t + NT * m] = widen(v[m]);
-    } else if constexpr (MODE == WR_U0) {
-        cx<double>* S = reinterpret_cast<cx<double>*>(a.S) + woff;
+        for (int m = 0; m < R; ++m) z[m] = src[NT * m];
+        block_fft<double, N2, +1, false, TW_AHEAD, false, true>(z, d0, d1, tw2_64, t);
 #pragma unroll
         for (int m = 0; m < R; ++m) {
-            const cx<double> u0 = widen(rot<+1>(scale(v[m], T(a.half_d0))));
-            for (int s = 0; s < a.n_iter; ++s) S[(size_t)s * Ntot + base + t + NT * m] = u0;
-        }
-    } else if constexpr (MODE == WR_NODE_OUT) {
-        cx<double>* S = reinterpret_cast<cx<double>*>(a.S) + (size_t)a.s * Ntot + woff;
-        cx<T>* cur = static_cast<cx<T>*>(a.cur) + woff;
-        const cx<T>* ph = static_cast<const cx<T>*>(a.ph);
-        const T dl = T(a.dl);
-        const bool need_next = (a.s < a.n_iter - 1) || a.last_node;
-        const bool final_sum = a.last_node && (a.s == a.n_iter - 1);
-#pragma unroll
-        for (int m = 0; m < R; ++m) {
-#pragma clang fp contract(off)
-            const size_t i = base + t + NT * m;
-            const cx<double> u = widen(rot<+1>(scale(cmulc(v[m], ph[i]), dl)));
-            if (need_next) {
-                const cx<double> nxt = psi0[i] + (S[i] + scale(u, 0.5));
-                if (final_sum) psi0[i] = nxt;
-                else cur[i] = narrow<T>(nxt);
-            }
-            if (!a.last_node) S[i] = S[i] + u;
+            psi0[NT * m] = z[m];
+            v[m] = narrow<T>(z[m]);
         }
     } else {
-        // WR_NODE_IN / WR_FINAL: spectral product, inverse row pass, twiddle
+        const cx<T>* src = static_cast<const cx<T>*>(a.src) + woff + base;
+#pragma unroll
+        for (int m = 0; m < R; ++m) v[m] = src[NT * m];
+        block_fft<T, N2, +1, DBUF, TW_AHEAD, false, true>(v, b0, b1, tw2, t);
+    }
+    cx<T>* u0 = static_cast<cx<T>*>(a.u0) + woff + base;
+    if constexpr (MODE == WR_U0) {
+#pragma unroll
+        for (int m = 0; m < R; ++m) u0[NT * m] = rot<+1>(scale(v[m], T(a.half_d0)));
+        return;
+    }
+    if constexpr (MODE == WR_NODE || MODE == WR_LAST) {
+#pragma clang fp contract(off)
+        cx<double>* S = reinterpret_cast<cx<double>*>(a.S) + woff + base;
+        const cx<T>* ph = static_cast<const cx<T>*>(a.ph) + base;
 #pragma unroll
         for (int m = 0; m < R; ++m) {
-            const size_t i = base + t + NT * m;
-            if constexpr (MODE == WR_NODE_IN) {
-                const cx<T> x = a.first ? narrow<T>(psi0[i]) : static_cast<const cx<T>*>(a.cur)[woff + i];
-                v[m] = cmul(x, static_cast<const cx<T>*>(a.ph)[i]);
+            const cx<double> u = widen(rot<+1>(cmulc(v[m], ph[NT * m])));
+            const cx<double> s = a.first_node ? widen(u0[NT * m]) : S[NT * m];
+            const cx<double> p0 = psi0[NT * m];
+            const cx<double> nxt = p0 + (s + scale(u, 0.5));
+            if constexpr (MODE == WR_LAST) {
+                z[m] = nxt;
             } else {
-                v[m] = scale(cmul(psi0[i], static_cast<const cx<double>*>(a.ph_last)[i]), a.out_scale);
+                // the last sweep's psi is needed at node M only (WR_LAST)
+                v[m] = a.last_sweep ? narrow<T>(p0) : narrow<T>(nxt);
+                if (!a.last_node) S[NT * m] = s + u;
             }
         }
-        block_fft<TP, N2, -1, false, TW_AHEAD>(v, my, my1, tw, t);
-        cx<TP>* dst = static_cast<cx<TP>*>(a.dst) + woff;
+    }
+    if constexpr (MODE == WR_LAST) {
+        const cx<double>* pl = static_cast<const cx<double>*>(a.ph_last) + base;
 #pragma unroll
-        for (int m = 0; m < R; ++m) {
-            const int n2 = t + NT * m;
-            cx<TP> w;
-            if constexpr (sizeof(TP) == 8) w = wN(twl64, twh64, split, (long long)n2 * k1);
-            else w = wN(twl, twh, split, (long long)n2 * k1);
-            dst[base + n2] = cmulc(v[m], w);
-        }
+        for (int m = 0; m < R; ++m) z[m] = scale(cmul(z[m], pl[NT * m]), a.out_scale);
+        block_fft<double, N2, -1, false, TW_AHEAD, false, true>(z, d0, d1, tw2_64, t);
+        cx<double>* dst = static_cast<cx<double>*>(a.dst) + woff + base;
+        Powers<double> w(twl64, twh64, split, k1, t, NT);
+#pragma unroll
+        for (int m = 0; m < R; ++m) dst[NT * m] = cmulc(z[m], w.next());
+    } else {
+        const cx<T>* ph = static_cast<const cx<T>*>(a.ph_next) + base;
+#pragma unroll
+        for (int m = 0; m < R; ++m) v[m] = cmul(v[m], ph[NT * m]);
+        block_fft<T, N2, -1, DBUF, TW_AHEAD, false, true>(v, b0, b1, tw2, t);
+        cx<T>* dst = static_cast<cx<T>*>(a.dst) + woff + base;
+        Powers<T> w(twl64, twh64, split, k1, t, NT);
+#pragma unroll
+        for (int m = 0; m < R; ++m) dst[NT * m] = cmulc(v[m], w.next());
     }
 }
 
@@ -242,36 +289,41 @@ __global__ void win_stitch_kernel(const cx<double>* __restrict__ win, cx<T>* __r
 
 // ---- launchers -------------------------------------------------------------------
 
-template <int N1>
-constexpr int col_tile() { return (COL_POINTS / N1) > 16 ? 16 : ((COL_POINTS / N1) < 1 ? 1 : (COL_POINTS / N1)); }
+// Columns per workgroup: 2048 points, or 4096 (32-byte row segments) for FP32
+// columns of 1024.  Long step at 2^22 modes, M = 4, two sweeps, 2048 / 4096 / 8192
+// points: FP32 859 / 803 / 824 us, FP64 1275 / 1315 / 1317; 2^18 modes (512-point
+// columns) FP32 131 / 139 / 162, FP64 164 / 187 / 231.
+template <typename TK, int N1>
+constexpr int col_tile() {
+    constexpr int points = sizeof(TK) == 4 && N1 >= 1024 ? 4096 : 2048;
+    return points / N1 > 16 ? 16 : points / N1;
+}
 
 template <int N2>
 constexpr int row_tile() { return (ROW_THREADS * WP / N2) > 1 ? (ROW_THREADS * WP / N2) : 1; }
 
 template <typename TIN, typename TK, typename TOUT, int MODE, int N1>
-static hipError_t cols_n1(const WindowStepArgs& w, const void* src, void* dst, const void* tw1, const void* twl,
-                          const void* twh, double cnode) {
-    constexpr int TC = col_tile<N1>();
+static hipError_t cols_n1(const WindowStepArgs& w, const void* src, void* dst, const void* tw1, double cnode,
+                          double dnode) {
+    constexpr int TC = col_tile<TK, N1>();
     if (w.n2 % TC) return hipErrorInvalidValue;
     hipLaunchKernelGGL((win_cols_kernel<TIN, TK, TOUT, N1, TC, MODE>), dim3(w.n2 / TC, w.windows), dim3(TC * N1 / WP), 0,
                        w.stream, static_cast<const cx<TIN>*>(src), static_cast<cx<TOUT>*>(dst), w.n2,
-                       static_cast<const cx<TK>*>(tw1), static_cast<const cx<TK>*>(twl),
-                       static_cast<const cx<TK>*>(twh), w.split, TK(cnode));
+                       static_cast<const cx<TK>*>(tw1), static_cast<const cx<double>*>(w.twl_64),
+                       static_cast<const cx<double>*>(w.twh_64), w.split, TK(cnode), TK(dnode));
     return hipGetLastError();
 }
 
 template <typename TIN, typename TK, typename TOUT, int MODE>
-static hipError_t cols(const WindowStepArgs& w, const void* src, void* dst, double cnode = 1.0) {
-    const bool f64 = sizeof(TK) == 8;
-    const void* tw1 = f64 ? w.tw1_64 : w.tw1;
-    const void* twl = f64 ? w.twl_64 : w.twl;
-    const void* twh = f64 ? w.twh_64 : w.twh;
+static hipError_t cols(const WindowStepArgs& w, const void* src, void* dst, double cnode = 1.0,
+                       double dnode = 1.0) {
+    const void* tw1 = sizeof(TK) == 8 ? w.tw1_64 : w.tw1;
     switch (w.n1) {
-        case 64: return cols_n1<TIN, TK, TOUT, MODE, 64>(w, src, dst, tw1, twl, twh, cnode);
-        case 128: return cols_n1<TIN, TK, TOUT, MODE, 128>(w, src, dst, tw1, twl, twh, cnode);
-        case 256: return cols_n1<TIN, TK, TOUT, MODE, 256>(w, src, dst, tw1, twl, twh, cnode);
-        case 512: return cols_n1<TIN, TK, TOUT, MODE, 512>(w, src, dst, tw1, twl, twh, cnode);
-        case 1024: return cols_n1<TIN, TK, TOUT, MODE, 1024>(w, src, dst, tw1, twl, twh, cnode);
+        case 64: return cols_n1<TIN, TK, TOUT, MODE, 64>(w, src, dst, tw1, cnode, dnode);
+        case 128: return cols_n1<TIN, TK, TOUT, MODE, 128>(w, src, dst, tw1, cnode, dnode);
+        case 256: return cols_n1<TIN, TK, TOUT, MODE, 256>(w, src, dst, tw1, cnode, dnode);
+        case 512: return cols_n1<TIN, TK, TOUT, MODE, 512>(w, src, dst, tw1, cnode, dnode);
+        case 1024: return cols_n1<TIN, TK, TOUT, MODE, 1024>(w, src, dst, tw1, cnode, dnode);
         default: return hipErrorInvalidValue;
     }
 }
@@ -282,9 +334,8 @@ static hipError_t rows_n2(const WindowStepArgs& w, const WinRowArgs& a) {
     if (w.n1 % TR) return hipErrorInvalidValue;
     hipLaunchKernelGGL((win_rows_kernel<T, N2, TR, MODE>), dim3(w.n1 / TR, w.windows), dim3(TR * N2 / WP), 0, w.stream, a,
                        static_cast<const cx<T>*>(w.tw2), static_cast<const cx<double>*>(w.tw2_64),
-                       static_cast<const cx<T>*>(w.twl), static_cast<const cx<T>*>(w.twh),
                        static_cast<const cx<double>*>(w.twl_64), static_cast<const cx<double>*>(w.twh_64), w.split,
-                       (long long)w.n, (long long)w.n * w.windows);
+                       (long long)w.n);
     return hipGetLastError();
 }
 
@@ -309,11 +360,10 @@ static hipError_t window_step_t(const WindowStepArgs& w) {
     if (w.windows < 1 || (!w.blocked && (w.windows != 1 || w.n_field != w.n))) return hipErrorInvalidValue;
     WinRowArgs a{};
     a.psi0 = static_cast<double*>(w.psi0);
-    a.S = static_cast<double*>(w.sums);
-    a.cur = w.cur;
-    a.n_iter = w.n_iter;
+    a.u0 = w.cur;
     const double* ns = w.node_scale_host;           // c_j, e_j as built (FP64), rounded to T below
-    // init: psi_0 = F[A] (FP64), U_0 / 2 into every S^(s)
+    const auto phase = [&](int l) { return static_cast<const char*>(w.phase) + (size_t)l * N * sizeof(cx<T>); };
+    // init: U_0 / 2 = i sigma dz / 2 F[|A|^2 A], psi_0 = F[A] (FP64)
     if (w.blocked) {
         // the tapered windows in FP64; the cube's column pass reads them before the
         // forward column pass overwrites them in place
@@ -326,33 +376,36 @@ static hipError_t window_step_t(const WindowStepArgs& w) {
         if ((e = cols<double, T, T, WC_FWD_CUBE>(w, w.work64, w.work))) return e;
         if ((e = cols<double, double, double, WC_FWD>(w, w.work64, w.work64))) return e;
     } else {
+        if ((e = cols<T, T, T, WC_FWD_CUBE>(w, w.in, w.work))) return e;
         if ((e = cols<T, double, double, WC_FWD>(w, w.in, w.work64))) return e;
     }
-    a.src = w.work64;
-    if ((e = rows<T, WR_PSI0>(w, a))) return e;
-    if (!w.blocked && (e = cols<T, T, T, WC_FWD_CUBE>(w, w.in, w.work))) return e;
     a.src = w.work;
     a.half_d0 = double(T(T(w.sigma) * T(ns[1])) * T(0.5));
     if ((e = rows<T, WR_U0>(w, a))) return e;
+    a.src = w.work64;
+    a.dst = w.work;
+    a.ph_next = phase(1);
+    if ((e = rows<T, WR_FIRST>(w, a))) return e;
+    a.src = w.work;
     for (int l = 1; l <= w.M; ++l) {
-        a.ph = static_cast<const char*>(w.phase) + (size_t)l * N * sizeof(cx<T>);
-        a.dl = double(T(w.sigma) * T(ns[2 * l + 1]));
-        a.last_node = (l == w.M);
+        const double cl = T(ns[2 * l]), dl = T(w.sigma) * T(ns[2 * l + 1]);
+        a.ph = phase(l);
+        a.first_node = l == 1;
+        a.last_node = l == w.M;
         for (int s = 0; s < w.n_iter; ++s) {
-            a.s = s;
-            a.first = (s == 0);
-            a.dst = w.work;
-            if ((e = rows<T, WR_NODE_IN>(w, a))) return e;
-            if ((e = cols<T, T, T, WC_NODE>(w, w.work, w.work, double(T(ns[2 * l]))))) return e;
-            a.src = w.work;
-            if ((e = rows<T, WR_NODE_OUT>(w, a))) return e;
+            if ((e = cols<T, T, T, WC_NODE>(w, w.work, w.work, cl, dl))) return e;
+            a.S = static_cast<double*>(w.sums) + (size_t)s * 2 * N * w.windows;
+            a.last_sweep = s == w.n_iter - 1;
+            if (a.last_sweep && a.last_node) break;
+            a.ph_next = phase(a.last_sweep ? l + 1 : l);
+            if ((e = rows<T, WR_NODE>(w, a))) return e;
         }
     }
     // final: A(z0 + L) from psi_M (FP64)
     a.ph_last = w.phase_last;
     a.out_scale = w.out_scale;
     a.dst = w.work64;
-    if ((e = rows<T, WR_FINAL>(w, a))) return e;
+    if ((e = rows<T, WR_LAST>(w, a))) return e;
     if (!w.blocked) return cols<double, double, T, WC_INV>(w, w.work64, w.out);
     if ((e = cols<double, double, double, WC_INV>(w, w.work64, w.work64))) return e;
     const unsigned grid = (unsigned)std::min<long long>((w.n_field + 255) / 256, 8192);
