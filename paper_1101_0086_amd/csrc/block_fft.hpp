@@ -272,6 +272,49 @@ __device__ __forceinline__ void load_twiddles(Twiddles<T, B>& t, const cx<T>* __
     all_twiddles<T, B, 1, n_passes(B)>(t.w, tw, tid);
 }
 
+// The pieces of a pass.  Reads are issued in the order the butterflies take
+// them.  FP32 reads of 2048 points or more form their addresses separately:
+// with common ones the compiler pairs neighbouring reads, and the first
+// butterflies wait for more of them (292 against 287 us a long step at 2^22
+// modes; at 1024 points the paired form is the faster one by 0.7 %).
+template <typename T, int B, bool LEAN>
+__device__ __forceinline__ void pass_read(cx<T> (&v)[8], cx<T>* in, int tid) {
+    constexpr int NT = B / 8;
+    constexpr int order[8] = {0, 4, 2, 6, 1, 5, 3, 7};
+    const int a = lds_base<T, LEAN>(tid);
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        const int m = order[q];
+        if constexpr (sizeof(T) == 4 && B >= 2048 && !LEAN) v[m] = in[lds_slot<T>(tid + NT * m)];
+        else v[m] = lds_at<T>(in, a, NT * m);
+    }
+}
+
+template <typename T, int B, int S, bool LEAN>
+__device__ __forceinline__ void pass_write(const cx<T> (&v)[8], cx<T>* out, int tid) {
+    constexpr int p = pass_span(B, S);
+    const int k = tid & (p - 1);
+    const int a = lds_base<T, LEAN>((tid - k) * 8 + k);
+#pragma unroll
+    for (int q = 0; q < 8; ++q) lds_at<T>(out, a, q * p) = v[q];
+}
+
+// the first pass: no twiddles, 8 / r butterflies of radix r
+template <typename T, int B, int SIGN, bool LEAN>
+__device__ __forceinline__ void pass_first(const cx<T> (&v)[8], cx<T>* out, int tid) {
+    constexpr int NT = B / 8, r = first_radix(B), NB = 8 / r;
+    const int a = lds_base<T, LEAN>(tid * r);
+#pragma unroll
+    for (int u = 0; u < NB; ++u) {
+        cx<T> x[r];
+#pragma unroll
+        for (int q = 0; q < r; ++q) x[q] = v[u + q * NB];
+        dft<SIGN, r>(x);
+#pragma unroll
+        for (int q = 0; q < r; ++q) lds_at<T>(out, a, u * NT * r + q) = x[q];
+    }
+}
+
 template <typename T, int B, int SIGN, int S, int NP, bool DBUF, int TWS, bool LEAN, bool EXACT8>
 __device__ __forceinline__ void passes(cx<T> (&v)[8], cx<T>* buf0, cx<T>* buf1, PassTw<T> (&wall)[NP - 1],
                                        const cx<T>* __restrict__ tw, const cx<T>* tl, int tid) {
@@ -281,7 +324,6 @@ __device__ __forceinline__ void passes(cx<T> (&v)[8], cx<T>* buf0, cx<T>* buf1, 
         if constexpr (S == 0) pass_twiddles<T, B, 1, EXACT8>(wall[0], tw, t);
         if constexpr (S + 2 < NP) pass_twiddles<T, B, S + 2, EXACT8>(wall[S + 1], tw, t);
     }
-    constexpr int NT = B / 8;
     constexpr int p = pass_span(B, S);
     constexpr bool first = (S == 0), last = (S == NP - 1);
     // exchange buffers: alternating (DBUF, pass S reads buf[(S - 1) % 2] and
@@ -289,26 +331,10 @@ __device__ __forceinline__ void passes(cx<T> (&v)[8], cx<T>* buf0, cx<T>* buf1, 
     cx<T>* in = DBUF ? ((S % 2) ? buf0 : buf1) : buf0;
     cx<T>* out = DBUF ? ((S % 2) ? buf1 : buf0) : buf0;
     if constexpr (first) {
-        constexpr int r = first_radix(B);
-        constexpr int NB = 8 / r;
-#pragma unroll
-        for (int u = 0; u < NB; ++u) {
-            cx<T> x[r];
-#pragma unroll
-            for (int q = 0; q < r; ++q) x[q] = v[u + q * NB];
-            dft<SIGN, r>(x);
-            const int a = lds_base<T, LEAN>(tid * r);
-#pragma unroll
-            for (int q = 0; q < r; ++q) lds_at<T>(out, a, u * NT * r + q) = x[q];
-        }
+        pass_first<T, B, SIGN, LEAN>(v, out, tid);
     } else {
         __syncthreads();        // the previous pass's writes are visible
-        const int ar = lds_base<T, LEAN>(tid);
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            constexpr int order[8] = {0, 4, 2, 6, 1, 5, 3, 7};   // the order the butterflies take them in
-            v[order[q]] = lds_at<T>(in, ar, NT * order[q]);
-        }
+        pass_read<T, B, LEAN>(v, in, tid);
         if constexpr (!DBUF) {
             // every read done before this pass overwrites.  The values are pinned in front
             // of the barrier: with a branch after the transform the compiler sank the last
@@ -335,12 +361,7 @@ __device__ __forceinline__ void passes(cx<T> (&v)[8], cx<T>* buf0, cx<T>* buf1, 
             else w.w8 = eighth(w.w1);
         }
         dft8_tw<SIGN>(v, w);
-        if constexpr (!last) {
-            const int k = tid & (p - 1);
-            const int a = lds_base<T, LEAN>((tid - k) * 8 + k);
-#pragma unroll
-            for (int q = 0; q < 8; ++q) lds_at<T>(out, a, q * p) = v[q];
-        }
+        if constexpr (!last) pass_write<T, B, S, LEAN>(v, out, tid);
     }
     if constexpr (!last) passes<T, B, SIGN, S + 1, NP, DBUF, TWS, LEAN, EXACT8>(v, buf0, buf1, wall, tw, tl, tid);
 }
@@ -375,6 +396,49 @@ __device__ __forceinline__ void block_fft(cx<T> (&v)[8], cx<T>*& buf0, cx<T>*& b
         cx<T>* s = buf0;
         buf0 = buf1;
         buf1 = s;
+    }
+}
+
+// ---- two transforms side by side --------------------------------------------------
+// Two independent B-point transforms of one workgroup, pass by pass with one
+// barrier for both, each between two buffers of its own (as DBUF): the second
+// one's reads are in flight under the first one's butterflies, and the first
+// one's writes under the second's.
+template <typename T, int B, int SA, int SB, int S, int NP>
+__device__ __forceinline__ void pair_passes(cx<T> (&va)[8], cx<T> (&vb)[8], cx<T>* a0, cx<T>* a1, cx<T>* b0, cx<T>* b1,
+                                            const PassTw<T> (&w)[NP - 1], int tid) {
+    constexpr bool last = (S == NP - 1);
+    // at 4096 points the reads share one address: the separate ones spill (272 against
+    // 265 us a long step at 2^22 modes; 13.5 against 13.7 at 2^15, 1024 points)
+    constexpr bool SHARED = B >= 4096;
+    if constexpr (S == 0) {
+        pass_first<T, B, SA, false>(va, a0, tid);
+        pass_first<T, B, SB, false>(vb, b0, tid);
+    } else {
+        __syncthreads();
+        pass_read<T, B, SHARED>(va, (S % 2) ? a0 : a1, tid);
+        pass_read<T, B, SHARED>(vb, (S % 2) ? b0 : b1, tid);
+        dft8_tw<SA>(va, w[S - 1]);
+        if constexpr (!last) pass_write<T, B, S, false>(va, (S % 2) ? a1 : a0, tid);
+        dft8_tw<SB>(vb, w[S - 1]);
+        if constexpr (!last) pass_write<T, B, S, false>(vb, (S % 2) ? b1 : b0, tid);
+    }
+    if constexpr (!last) pair_passes<T, B, SA, SB, S + 1, NP>(va, vb, a0, a1, b0, b1, w, tid);
+}
+
+// The buffers of both are swapped on return as block_fft's are.
+template <typename T, int B, int SA, int SB>
+__device__ __forceinline__ void block_fft_pair(cx<T> (&va)[8], cx<T> (&vb)[8], cx<T>*& a0, cx<T>*& a1, cx<T>*& b0,
+                                               cx<T>*& b1, const Twiddles<T, B>& regs, int tid) {
+    constexpr int NP = n_passes(B);
+    pair_passes<T, B, SA, SB, 0, NP>(va, vb, a0, a1, b0, b1, regs.w, tid);
+    if constexpr ((NP - 1) % 2 == 1) {
+        cx<T>* s = a0;
+        a0 = a1;
+        a1 = s;
+        s = b0;
+        b0 = b1;
+        b1 = s;
     }
 }
 

@@ -73,8 +73,9 @@ struct StepTables {
 // 2.62 ms with 8-point DFTs behind seven twiddle products and the last node
 // selected per element, 2.29 ms with the passes of block_fft.hpp, the last
 // node behind a uniform branch and the node's two scales folded (1446 against
-// 1681 vector instructions per node); 2^18 modes in FP64 (NIT = 2): 84 against
-// 60 us per step with double-buffered transforms and an LDS twiddle table.
+// 1681 vector instructions per node), 2.11 ms with the evaluations in pairs;
+// 2^18 modes in FP64 (NIT = 2): 84 against 52 us per step with double-buffered
+// transforms and an LDS twiddle table.
 // Both kernels are held to 256 registers per lane (two waves per SIMD): at
 // B <= 2048 a workgroup has at most one wave per SIMD, and the compiler would
 // otherwise take up to 512 and keep one workgroup per CU.
