@@ -8,7 +8,7 @@
 //   sweep s one workgroup per (block, node l): steps 2-4 for node l = 1..M from
 //           psi^(s)_l (psi^(0)_l = psi_0), storing U^(s)_l; in sweep 0 one more
 //           per block computes U_0 / 2 = i sigma dz F[|A_0|^2 A_0] / 2, which
-//           only the sums need
+//           only the sums need (many blocks: init does)
 //   final   one workgroup per block: step 7 from psi^(n_iter)_M, scatter of the core.
 // psi^(s+1)_l = psi_0 + U_0/2 + sum_{0<j<l} U_j + U_l/2 (Eq. 6, FP64, left to
 // right) is added up by the workgroup that needs it (NP_OWN), or, where those
@@ -37,7 +37,7 @@ namespace {
 
 constexpr int PTS = 8;
 constexpr int XCDS = 8;
-constexpr int NODE_DBUF_GROUPS = 256;   // node workgroups up to which each has a CU of its own
+constexpr int NODE_DBUF_GROUPS = 256;   // workgroups up to which each has a CU of its own
 
 template <typename T>
 __device__ __forceinline__ cx<double> widen(cx<T> a) { return {double(a.re), double(a.im)}; }
@@ -60,24 +60,39 @@ __device__ __forceinline__ cx<double> window_sample(const cx<T>* __restrict__ in
     return scale(widen(in[wrap(w0 + t, n)]), taper[t]);
 }
 
-template <typename T, int B>
+// FEW (a CU for every block): psi_0 alone, two exchange buffers; else U_0 / 2 too and one
+// buffer (two workgroups of 4096 points per CU instead of one).
+template <typename T, int B, bool FEW>
 __global__ void __launch_bounds__(B / PTS)
-np_init_kernel(const cx<T>* __restrict__ in, cx<double>* __restrict__ psi0_buf, long long n, int core, int lead,
-               const cx<double>* __restrict__ tw64, const double* __restrict__ taper) {
+np_init_kernel(const cx<T>* __restrict__ in, cx<double>* __restrict__ psi0_buf, cx<T>* __restrict__ h0_buf,
+               long long n, int core, int lead, const T* __restrict__ node_scale, const cx<T>* __restrict__ tw,
+               const cx<double>* __restrict__ tw64, const double* __restrict__ taper, T sigma) {
     constexpr int R = PTS;
     constexpr int NT = B / R;
-    __shared__ cx<double> lds64[2 * B];
+    __shared__ cx<double> lds64[(FEW ? 2 : 1) * B];
     const int tid = threadIdx.x;
     const long long w0 = (long long)blockIdx.x * core - lead;
     cx<double> psi0[R];
+    cx<T> cur[R];
 #pragma unroll
-    for (int m = 0; m < R; ++m) psi0[m] = window_sample(in, taper, w0, tid + NT * m, n);
+    for (int m = 0; m < R; ++m) {
+        psi0[m] = window_sample(in, taper, w0, tid + NT * m, n);
+        if constexpr (!FEW) cur[m] = narrow<T>(scale(psi0[m], norm2(psi0[m])));
+    }
     cx<double>* e0 = lds64;
-    cx<double>* e1 = lds64 + B;
-    block_fft<double, B, +1, true, TW_AHEAD>(psi0, e0, e1, tw64, tid);
+    cx<double>* e1 = lds64 + (FEW ? B : 0);
+    block_fft<double, B, +1, FEW, TW_AHEAD>(psi0, e0, e1, tw64, tid);
     const size_t base = (size_t)blockIdx.x * B;
 #pragma unroll
     for (int m = 0; m < R; ++m) psi0_buf[base + tid + NT * m] = psi0[m];
+    if constexpr (!FEW) {
+        cx<T>* l0 = reinterpret_cast<cx<T>*>(lds64);
+        cx<T>* l1 = l0;
+        block_fft<T, B, +1, false, TW_AHEAD>(cur, l0, l1, tw, tid);
+        const T d0 = sigma * node_scale[1];
+#pragma unroll
+        for (int m = 0; m < R; ++m) h0_buf[base + tid + NT * m] = rot<+1>(scale(cur[m], d0 * T(0.5)));
+    }
 }
 
 // psi_0 + (U_0/2 + U_1 + ... + U_{l-1} + U_l/2), summed left to right in FP64; the
@@ -103,8 +118,8 @@ __device__ __forceinline__ void trapezoid(cx<double> (&v)[PTS], const cx<double>
     }
 }
 
-// NP_FIRST (sweep 0): nodes 0..M, psi^(0)_l = psi_0, node 0 computes U_0 / 2 into h0_buf;
-// else nodes 1..M, psi^(s)_l from the last sweep's increments `prev` (NP_OWN) or from
+// NP_FIRST (sweep 0): nodes first..M, psi^(0)_l = psi_0, node 0 computes U_0 / 2 into
+// h0_buf (first = 1: np_init_kernel has); else nodes 1..M, psi^(s)_l from the last sweep's increments `prev` (NP_OWN) or from
 // `prev` itself (NP_SUMMED).  Two exchange buffers (one barrier per exchange) when DBUF,
 // else one (three workgroups of 4096 FP32 points per CU instead of one).
 enum NodeMode { NP_FIRST = 0, NP_OWN = 1, NP_SUMMED = 2 };
@@ -114,14 +129,14 @@ __global__ void __launch_bounds__(B / PTS)
 np_node_kernel(const cx<T>* __restrict__ in, const cx<double>* __restrict__ psi0_buf, cx<T>* __restrict__ h0_buf,
                const cx<T>* __restrict__ prev, cx<T>* __restrict__ u_buf, int n_blocks, long long n, int core,
                int lead, const cx<T>* __restrict__ phase, const T* __restrict__ node_scale,
-               const cx<T>* __restrict__ tw, const double* __restrict__ taper, int M, T sigma) {
+               const cx<T>* __restrict__ tw, const double* __restrict__ taper, int M, int first, T sigma) {
     constexpr int R = PTS;
     constexpr int NT = B / R;
     constexpr bool FIRST = MODE == NP_FIRST;
     const int xcd = blockIdx.x % XCDS;
     const int k = blockIdx.x / XCDS;
-    const int nodes = FIRST ? M + 1 : M;
-    const int l = FIRST ? k % nodes : k % nodes + 1;
+    const int nodes = M + 1 - first;              // nodes first..M (first = 1 after sweep 0)
+    const int l = k % nodes + first;
     const int b = (k / nodes) * XCDS + xcd;
     if (b >= n_blocks) return;                    // the whole workgroup leaves together
     __shared__ cx<T> lds[(DBUF ? 2 : 1) * B];
@@ -212,7 +227,7 @@ np_sum_kernel(cx<double>* __restrict__ psi0_buf, const cx<T>* __restrict__ h0_bu
 }
 
 // OWN: psi^(n_iter)_M from the last sweep's increments u_buf, else in psi0_buf (np_sum_kernel)
-template <typename T, int B, bool OWN>
+template <typename T, int B, bool OWN, bool FEW>
 __global__ void __launch_bounds__(B / PTS)
 np_final_kernel(const cx<double>* __restrict__ psi0_buf, const cx<T>* __restrict__ h0_buf,
                 const cx<T>* __restrict__ u_buf, cx<T>* __restrict__ out, long long n, int core, int lead,
@@ -220,7 +235,7 @@ np_final_kernel(const cx<double>* __restrict__ psi0_buf, const cx<T>* __restrict
                 double out_scale) {
     constexpr int R = PTS;
     constexpr int NT = B / R;
-    __shared__ cx<double> lds64[2 * B];
+    __shared__ cx<double> lds64[(FEW ? 2 : 1) * B];
     const int tid = threadIdx.x;
     const int b = blockIdx.x;
     const size_t base = (size_t)b * B;
@@ -235,8 +250,8 @@ np_final_kernel(const cx<double>* __restrict__ psi0_buf, const cx<T>* __restrict
 #pragma unroll
     for (int m = 0; m < R; ++m) v[m] = scale(cmul(v[m], phase_last[tid + NT * m]), out_scale);
     cx<double>* e0 = lds64;
-    cx<double>* e1 = lds64 + B;
-    block_fft<double, B, -1, true, TW_AHEAD>(v, e0, e1, tw64, tid);
+    cx<double>* e1 = lds64 + (FEW ? B : 0);
+    block_fft<double, B, -1, FEW, TW_AHEAD>(v, e0, e1, tw64, tid);
     const long long c0 = (long long)b * core;
     const long long rest = n - c0;
     const int clen = rest < core ? (int)rest : core;
@@ -248,15 +263,14 @@ np_final_kernel(const cx<double>* __restrict__ psi0_buf, const cx<T>* __restrict
 }
 
 template <typename T, int B, int MODE, bool DBUF>
-static void launch_sweep(const BlockStepArgs& a, const NodeBuffers& nb, const void* prev, void* u) {
-    const int nodes = MODE == NP_FIRST ? a.M + 1 : a.M;
-    const unsigned groups = (unsigned)(XCDS * nodes * ((a.n_blocks + XCDS - 1) / XCDS));
+static void launch_sweep(const BlockStepArgs& a, const NodeBuffers& nb, const void* prev, void* u, int first) {
+    const unsigned groups = (unsigned)(XCDS * (a.M + 1 - first) * ((a.n_blocks + XCDS - 1) / XCDS));
     hipLaunchKernelGGL((np_node_kernel<T, B, MODE, DBUF>), dim3(groups), dim3(B / PTS), 0, a.stream,
                        static_cast<const cx<T>*>(a.in), static_cast<const cx<double>*>(nb.psi0),
                        static_cast<cx<T>*>(nb.half_u0), static_cast<const cx<T>*>(prev), static_cast<cx<T>*>(u),
                        a.n_blocks, (long long)a.n, a.core, a.lead, static_cast<const cx<T>*>(a.phase),
                        static_cast<const T*>(a.node_scale), static_cast<const cx<T>*>(a.twiddle),
-                       static_cast<const double*>(a.taper), a.M, T(a.sigma));
+                       static_cast<const double*>(a.taper), a.M, first, T(a.sigma));
 }
 
 // Whether Eq. 6's sums get a launch of their own.  A node's workgroup that adds
@@ -278,8 +292,20 @@ static hipError_t node_step_typed(const BlockStepArgs& a) {
     auto* psi0 = static_cast<cx<double>*>(nb.psi0);
     const auto* h0 = static_cast<const cx<T>*>(nb.half_u0);
     const auto* tw64 = static_cast<const cx<double>*>(a.twiddle64);
-    hipLaunchKernelGGL((np_init_kernel<T, B>), dim3(a.n_blocks), threads, 0, a.stream, static_cast<const cx<T>*>(a.in),
-                       psi0, (long long)a.n, a.core, a.lead, tw64, static_cast<const double*>(a.taper));
+    // with a CU for every block, U_0 is node 0 of the first sweep, beside the others; with
+    // more it is computed with psi_0 (2^19 modes, 1024 blocks of 2048, M = 1, two sweeps:
+    // 66.7 us a long step as node 0, where every workgroup fills its twiddle table first,
+    // 59 with psi_0)
+    const bool few = a.n_blocks <= NODE_DBUF_GROUPS;
+    const int first = few ? 0 : 1;
+    const auto init = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(a.n_blocks), threads, 0, a.stream, static_cast<const cx<T>*>(a.in), psi0,
+                           static_cast<cx<T>*>(nb.half_u0), (long long)a.n, a.core, a.lead,
+                           static_cast<const T*>(a.node_scale), static_cast<const cx<T>*>(a.twiddle), tw64,
+                           static_cast<const double*>(a.taper), T(a.sigma));
+    };
+    if (few) init(np_init_kernel<T, B, true>);
+    else init(np_init_kernel<T, B, false>);
     const long long total = (long long)a.n_blocks * B;
     const dim3 sum_groups((unsigned)((total + SUM_TPB - 1) / SUM_TPB));
     const bool dbuf = (long long)a.n_blocks * (a.M + 1) <= NODE_DBUF_GROUPS;
@@ -291,9 +317,9 @@ static hipError_t node_step_typed(const BlockStepArgs& a) {
         void* u = apart ? nb.u[0] : nb.u[s & 1];
         const auto sweep = [&](auto db) {
             constexpr bool D = decltype(db)::value;
-            if (s == 0) launch_sweep<T, B, NP_FIRST, D>(a, nb, prev, u);
-            else if (apart) launch_sweep<T, B, NP_SUMMED, D>(a, nb, prev, u);
-            else launch_sweep<T, B, NP_OWN, D>(a, nb, prev, u);
+            if (s == 0) launch_sweep<T, B, NP_FIRST, D>(a, nb, prev, u, first);
+            else if (apart) launch_sweep<T, B, NP_SUMMED, D>(a, nb, prev, u, 1);
+            else launch_sweep<T, B, NP_OWN, D>(a, nb, prev, u, 1);
         };
         if (dbuf) sweep(std::true_type{});
         else sweep(std::false_type{});
@@ -311,8 +337,9 @@ static hipError_t node_step_typed(const BlockStepArgs& a) {
                            (long long)a.n, a.core, a.lead, static_cast<const cx<double>*>(a.phase_last), tw64, a.M,
                            a.out_scale);
     };
-    if (apart) final(np_final_kernel<T, B, false>);
-    else final(np_final_kernel<T, B, true>);
+    if (apart) final(np_final_kernel<T, B, false, true>);
+    else if (few) final(np_final_kernel<T, B, true, true>);
+    else final(np_final_kernel<T, B, true, false>);
     return hipGetLastError();
 }
 
