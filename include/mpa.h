@@ -294,8 +294,10 @@ int mpa_propagate_checkpointed(mpa_plan* plan, void* field, double z0, double z1
  * the inputs of the next segment are recomputed on a second stream of the
  * plan's while the current segment is reversed on `stream`, ordered by
  * events; the results are bitwise those of one stream).  The first call allocates a
- * workspace of n_blocks x (3 n_iter M + 2) x B complex samples plus the
- * kept step inputs, held by the plan until it is destroyed.  Deterministic:
+ * workspace of n_blocks x (3 n_iter M + 2) x B complex samples (for few
+ * blocks, whose steps' recomputes share launches, up to 16 times its
+ * 3 n_iter M + 1, at most 128 MiB) plus the kept step inputs, held by the
+ * plan until it is destroyed.  Deterministic:
  * per-block partial sums are added in a fixed order.                        */
 int mpa_adjoint(mpa_plan* plan, const void* checkpoints, void* grad, double z0, double z1,
                 double* param_grad, int64_t store_steps, void* stream);
@@ -356,8 +358,8 @@ int mpa_batch_propagate(mpa_batch_plan* plan, void* fields, double z0, double z1
  * mpa_adjoint on a plan of its own (sigma scaled, same parameters): the
  * kernels run the same per-block operations, with the work items walked by a
  * fixed grid of workgroups.  The workspace (held by the batch plan) is
- * grid x (3 n_iter M + 1) x block + work_items x block complex samples plus
- * the kept step inputs.                                                     */
+ * grid x (3 n_iter M + 1) x block (few work items: as mpa_adjoint's) +
+ * work_items x block complex samples plus the kept step inputs.                                                     */
 int mpa_batch_checkpoint_count(const mpa_batch_plan* plan, double z0, double z1, int64_t* count);
 int mpa_batch_propagate_checkpointed(mpa_batch_plan* plan, void* fields, double z0, double z1,
                                      void* checkpoints, void* stream);

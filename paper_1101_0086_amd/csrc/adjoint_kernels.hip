@@ -59,20 +59,28 @@ __device__ __forceinline__ long long wrap(long long g, long long n) {
 }
 
 // node-precision transform, double-buffered when DB, its twiddles read from
-// the LDS table `twl` in each pass
+// the LDS table `twl` in each pass: the products, whose lesser rounding the
+// parameter derivatives of FP32 plans show
 template <typename T, int B, int SG, bool DB>
 __device__ __forceinline__ void node_fft(cx<T> (&v)[PTS], cx<T>*& db0, cx<T>*& db1, cx<T>* lds,
                                          const cx<T>* __restrict__ tw, const cx<T>* twl, int tid) {
     if constexpr (DB) {
-        block_fft<T, B, SG, true, TW_TABLE>(v, db0, db1, tw, tid, nullptr, twl);
+        block_fft<T, B, SG, true, TW_PRODUCTS, true>(v, db0, db1, tw, tid, nullptr, twl);
     } else {
         cx<T>* l0 = lds;
         cx<T>* l1 = lds;
-        block_fft<T, B, SG, false, TW_TABLE>(v, l0, l1, tw, tid, nullptr, twl);
+        block_fft<T, B, SG, false, TW_PRODUCTS, true>(v, l0, l1, tw, tid, nullptr, twl);
     }
 }
 
 }  // namespace
+
+// The two halves of a reverse step, in one launch or apart (AdjointPart in
+// launch.hpp).  The recompute of a long step needs its input alone, not the
+// gradient, so where a step's work items leave most of the chip idle the
+// recomputes of several steps run side by side in one launch (item w of it:
+// step w / n_items, inputs in_stride samples apart, a node store of its own),
+// and only the reverse halves follow one another.
 
 // One workgroup per work item.  A single field (items == nullptr): item w is
 // block w of the field.  Many fields of different lengths concatenated (as in
@@ -91,25 +99,34 @@ __device__ __forceinline__ void node_fft(cx<T> (&v)[PTS], cx<T>*& db0, cx<T>*& d
 // workgroup per CU; 102 spilled at B = 4096), and gathered from the global
 // table in each pass they cost 30 % of a batched reverse long step; with the
 // table the kernel is held to 256 registers (two workgroups per CU at
-// B = 2048, a few registers spilled).
-template <typename T, int B, int NIT>
+// B = 2048).  Each access forms its LDS address (LEAN): kept over the node
+// loop they spilled 64 to 90 registers at two sweeps.  The reverse half is a
+// chain of 13 transforms (M = 2, two sweeps) bound by their latency: its stored
+// values are loaded a transform ahead of their use, and the derivatives'
+// omega^2, omega^3 are applied once at the end instead of at each evaluation
+// (54 to 33.5 us a launch of 43 blocks of 2048).
+template <typename T, int B, int NIT, int PART>
 __global__ void __launch_bounds__(B / PTS) __attribute__((amdgpu_waves_per_eu(2)))
 mpa_adjoint_block_kernel(const cx<T>* __restrict__ fin, const cx<double>* __restrict__ gin,
                          cx<double>* __restrict__ g_blk, double* __restrict__ partial,
                          cx<T>* __restrict__ node_store, cx<double>* __restrict__ last_store,
                          const int2* __restrict__ items, int n_items, const long long* __restrict__ offset,
                          const long long* __restrict__ len, const double* __restrict__ sigma_scale,
-                         long long n_field, int core, int lead, const cx<T>* __restrict__ phase,
+                         int steps, long long in_stride, long long n_field, int core, int lead, const cx<T>* __restrict__ phase,
                          const cx<double>* __restrict__ phase_last, const T* __restrict__ node_scale,
                          const cx<T>* __restrict__ tw, const cx<double>* __restrict__ tw64,
                          const double* __restrict__ taper, const cx<double>* __restrict__ mask_grad, int M,
                          const double* __restrict__ nw, double out_scale, double w1) {
     __shared__ cx<double> lds64[B];
-    __shared__ cx<T> twl[tl_elems<T>(B)];
-    fill_twiddle_table<T, B>(twl, tw, threadIdx.x, B / PTS);   // barrier: each item's first
-    cx<T>* __restrict__ store = node_store + (size_t)blockIdx.x * NIT * M * 3 * B;
-    cx<double>* __restrict__ last = last_store + (size_t)blockIdx.x * B;
-    for (int w = blockIdx.x; w < n_items; w += gridDim.x) {
+    __shared__ cx<T> twl[product_elems(B)];
+    fill_product_table<T, B>(twl, tw, threadIdx.x, B / PTS);   // barrier: each item's first
+    for (int ws = blockIdx.x; ws < n_items * steps; ws += gridDim.x) {
+        // one launch: the workgroup reuses its store for every item it takes; apart: every
+        // (step, item) has its own
+        const size_t own = PART == ADJ_WHOLE ? blockIdx.x : ws;
+        cx<T>* __restrict__ store = node_store + own * NIT * M * 3 * B;
+        cx<double>* __restrict__ last = last_store + own * B;
+        const int w = PART == ADJ_RECOMPUTE ? ws % n_items : ws;
         long long base = 0, n = n_field;
         int blk = w;
         double sc = 1.0;
@@ -120,7 +137,7 @@ mpa_adjoint_block_kernel(const cx<T>* __restrict__ fin, const cx<double>* __rest
             blk = it.y;
             sc = sigma_scale[it.x];
         }
-        const cx<T>* __restrict__ in = fin + base;
+        const cx<T>* __restrict__ in = fin + base + (PART == ADJ_RECOMPUTE ? ws / n_items * in_stride : 0);
         const cx<double>* __restrict__ g_out = gin + base;
         const long long c0 = (long long)blk * core;
         cx<double>* __restrict__ g_item = g_blk + (size_t)w * B;
@@ -225,25 +242,37 @@ template <typename T, int B>
 int adjoint_occupancy(int n_iter);
 
 #if !defined(MPA_SPLIT) || defined(MPA_PART_T)
-template <typename T, int B, int NIT>
-static hipError_t adjoint_typed(const AdjointStepArgs& a) {
+template <typename T, int B, int NIT, int PART>
+static hipError_t adjoint_part(const AdjointStepArgs& a) {
     const BatchItems* bt = a.batch;
     const int n_items = bt ? bt->n_items : a.n_blocks;
-    const int grid = bt ? a.grid : a.n_blocks;
-    if (grid < 1 || grid > n_items) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((mpa_adjoint_block_kernel<T, B, NIT>), dim3(grid), dim3(B / PTS), 0, a.stream,
+    const int steps = PART == ADJ_RECOMPUTE ? a.steps : 1;
+    const int grid = PART != ADJ_WHOLE ? n_items * steps : bt ? a.grid : a.n_blocks;
+    if (steps < 1 || grid < 1 || grid > n_items * steps) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((mpa_adjoint_block_kernel<T, B, NIT, PART>), dim3(grid), dim3(B / PTS), 0, a.stream,
                        static_cast<const cx<T>*>(a.in), static_cast<const cx<double>*>(a.g_out),
                        static_cast<cx<double>*>(a.g_blk), a.partial, static_cast<cx<T>*>(a.node_store),
                        static_cast<cx<double>*>(a.last_store), bt ? static_cast<const int2*>(bt->items) : nullptr,
                        n_items, bt ? static_cast<const long long*>(bt->offset) : nullptr,
                        bt ? static_cast<const long long*>(bt->len) : nullptr,
-                       bt ? static_cast<const double*>(bt->sigma_scale) : nullptr, (long long)a.n, a.core, a.lead,
+                       bt ? static_cast<const double*>(bt->sigma_scale) : nullptr, steps, (long long)a.in_stride,
+                       (long long)a.n, a.core, a.lead,
                        static_cast<const cx<T>*>(a.phase), static_cast<const cx<double>*>(a.phase_last),
                        static_cast<const T*>(a.node_scale), static_cast<const cx<T>*>(a.twiddle),
                        static_cast<const cx<double>*>(a.twiddle64), static_cast<const double*>(a.taper),
                        static_cast<const cx<double>*>(a.mask_grad), a.M, static_cast<const double*>(a.node_w),
                        a.out_scale, a.w1);
     return hipGetLastError();
+}
+
+template <typename T, int B, int NIT>
+static hipError_t adjoint_typed(const AdjointStepArgs& a) {
+    switch (a.part) {
+        case ADJ_WHOLE: return adjoint_part<T, B, NIT, ADJ_WHOLE>(a);
+        case ADJ_RECOMPUTE: return adjoint_part<T, B, NIT, ADJ_RECOMPUTE>(a);
+        case ADJ_REVERSE: return adjoint_part<T, B, NIT, ADJ_REVERSE>(a);
+        default: return hipErrorInvalidValue;
+    }
 }
 
 template <typename T, int B>
@@ -263,11 +292,11 @@ template <typename T, int B>
 int adjoint_occupancy(int n_iter) {
     const void* f = nullptr;
     switch (n_iter) {
-        case 1: f = reinterpret_cast<const void*>(&mpa_adjoint_block_kernel<T, B, 1>); break;
-        case 2: f = reinterpret_cast<const void*>(&mpa_adjoint_block_kernel<T, B, 2>); break;
-        case 3: f = reinterpret_cast<const void*>(&mpa_adjoint_block_kernel<T, B, 3>); break;
-        case 4: f = reinterpret_cast<const void*>(&mpa_adjoint_block_kernel<T, B, 4>); break;
-        case 5: f = reinterpret_cast<const void*>(&mpa_adjoint_block_kernel<T, B, 5>); break;
+        case 1: f = reinterpret_cast<const void*>(&mpa_adjoint_block_kernel<T, B, 1, ADJ_WHOLE>); break;
+        case 2: f = reinterpret_cast<const void*>(&mpa_adjoint_block_kernel<T, B, 2, ADJ_WHOLE>); break;
+        case 3: f = reinterpret_cast<const void*>(&mpa_adjoint_block_kernel<T, B, 3, ADJ_WHOLE>); break;
+        case 4: f = reinterpret_cast<const void*>(&mpa_adjoint_block_kernel<T, B, 4, ADJ_WHOLE>); break;
+        case 5: f = reinterpret_cast<const void*>(&mpa_adjoint_block_kernel<T, B, 5, ADJ_WHOLE>); break;
         default: return 0;
     }
     int n = 0;

@@ -58,13 +58,20 @@ hipError_t launch_node_parallel_step(const BlockStepArgs& a);
 hipError_t launch_copy_field(const void* src, void* dst, int64_t count, int precision, hipStream_t stream);
 
 // Reverse pass of one long step over every block of one field.
+// Which halves of a reverse step a launch runs: both, the forward recomputes of
+// `steps` long steps, or the reverse half from such a recompute's node store.
+enum AdjointPart { ADJ_WHOLE = 0, ADJ_RECOMPUTE = 1, ADJ_REVERSE = 2 };
+
 struct AdjointStepArgs {
+    int32_t part;            // AdjointPart
+    int32_t steps;           // ADJ_RECOMPUTE: long steps (same tables), node store step-major
+    int64_t in_stride;       // ADJ_RECOMPUTE: samples from one step's inputs to the next's
     const void* in;          // fields at z0 of the long step (plan precision)
     const void* g_out;       // FP64 complex: gradient with respect to the fields at z0 + L
     void* g_blk;             // FP64 complex, work items x B: each window's input gradient (tapered)
     double* partial;         // work items x 3: d/dsigma, d/dbeta2, d/dbeta3 of each item
-    void* node_store;        // workgroups x n_iter x M x 3 x B complex (plan precision)
-    void* last_store;        // workgroups x B FP64 complex
+    void* node_store;        // workgroups (ADJ_WHOLE) or steps x items, x n_iter x M x 3 x B complex
+    void* last_store;        // the same x B FP64 complex
     int64_t n;               // samples of the field (single field)
     int32_t block;
     int32_t lead;            // samples of each window before its core: halo + window shift

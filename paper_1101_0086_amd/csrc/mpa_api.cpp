@@ -226,8 +226,9 @@ struct DevBuf {
 
 // Reverse-pass workspace, allocated by the first reverse pass and grown as needed.
 struct AdjWork {
-    void* node = nullptr;       // workgroups x n_iter x M x 3 x B complex (plan precision)
-    void* last = nullptr;       // workgroups x B FP64 complex
+    void* node = nullptr;       // stores x n_iter x M x 3 x B complex (plan precision); stores: the reverse
+    void* last = nullptr;       // kernel's workgroups, or ahead x work items; `last`: stores x B FP64 complex
+    int32_t ahead = 1;          // long steps whose recomputes run in one launch (1: none)
     void* gblk = nullptr;       // work items x B FP64 complex
     void* partial = nullptr;    // work items x 3 doubles
     void* ga = nullptr;         // FP64 complex fields: the gradient carried between long steps
@@ -987,15 +988,55 @@ static int reserve_fields(const AdjTarget& t, void** buf, int64_t* cap, int64_t 
     return MPA_OK;
 }
 
+// Long steps whose forward recomputes run in one launch ahead of their reverse
+// halves (1: recompute and reverse in one kernel per step).  A step's recompute
+// does not wait for the gradient, so where the items of one step leave most of
+// the chip idle several steps' recomputes fill it, as many as are resident at
+// once and fit 128 MiB of node stores (they are read back from the last-level
+// cache).  Gradient of a 2^16-mode field, 43 blocks of 2048, two nodes, two sweeps:
+// 59 us a step in one kernel; apart 33.5 and 33.7 for the recomputes of eleven
+// steps.  Under four steps to a launch the second launch and the stores' trip
+// through the cache leave little of that.
+static int recompute_ahead(const mpa_plan* p, int64_t n_items, size_t per_store) {
+    int cus = 0;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, p->device) != hipSuccess || cus <= 0)
+        cus = 256;
+    const int per_cu = mpa::adjoint_workgroups_per_cu(p->prm.precision, p->block, p->prm.n_iter);
+    const int64_t resident = (int64_t)cus * (per_cu > 0 ? per_cu : 1);
+    const int64_t fit = (int64_t)(((size_t)128 << 20) / (per_store * (size_t)n_items));
+    const int64_t q = std::min<int64_t>({16, resident / n_items, fit});
+    return q >= 4 ? (int)q : 1;
+}
+
 // Fixed part of the reverse-pass workspace and the roll-off derivative tables.
 static int adjoint_setup(const AdjTarget& t) {
     mpa_plan* p = t.p;
     AdjWork* w = t.w;
     const int B = p->block, M = p->prm.M, nit = p->prm.n_iter, S = (int)p->beta2.size();
     if (!w->node) {
-        const size_t wg = (size_t)t.grid, ni = (size_t)t.n_items;
-        const bool ok = hipMalloc(&w->node, wg * nit * M * 3 * B * p->elem) == hipSuccess &&
-                        hipMalloc(&w->last, wg * B * 16) == hipSuccess &&
+        const size_t ni = (size_t)t.n_items;
+        size_t wg = (size_t)t.grid;
+        const size_t per_store = (size_t)B * ((size_t)nit * M * 3 * p->elem + 16);
+        const auto stores = [&]() {
+            return hipMalloc(&w->node, wg * nit * M * 3 * B * p->elem) == hipSuccess &&
+                   hipMalloc(&w->last, wg * B * 16) == hipSuccess;
+        };
+        w->ahead = recompute_ahead(p, t.n_items, per_store);
+        bool ok = false;
+        if (w->ahead > 1) {
+            wg = (size_t)w->ahead * ni;
+            ok = stores();
+            if (!ok) {                                // the one-launch form needs less
+                for (void** q : {&w->node, &w->last}) {
+                    if (*q) (void)hipFree(*q);
+                    *q = nullptr;
+                }
+                (void)hipGetLastError();
+                w->ahead = 1;
+                wg = (size_t)t.grid;
+            }
+        }
+        ok = (ok || stores()) &&
                         hipMalloc(&w->gblk, ni * B * 16) == hipSuccess &&
                         hipMalloc(&w->partial, ni * 3 * sizeof(double)) == hipSuccess &&
                         hipMalloc(&w->ga, (size_t)t.count * 16) == hipSuccess &&
@@ -1091,46 +1132,41 @@ static int adjoint_setup(const AdjTarget& t) {
     return MPA_OK;
 }
 
+// The parts of a reverse step's arguments that its recompute needs too.
+struct AdjRows {
+    int s, ns_row;                  // table row (span or boundary-crossing step), node-scale row
+    bool operator==(const AdjRows& o) const { return s == o.s && ns_row == o.ns_row; }
+};
+
+static AdjRows adjoint_rows(const mpa_plan* p, int64_t m) {
+    const int s = p->sched.span_of(m);
+    // a boundary-crossing step's own node-scale row carries sigma_j; the reverse kernel
+    // takes sigma_j from the node weights and the row without it
+    return {s, s < (int)p->beta2.size() ? gain_row(p, m, s) : plain_row(p, m)};
+}
+
 // Reverse pass of long step m: g_in (FP64) from g_out (FP64), adding the
 // step's parameter derivatives to param_grad.  A step across span boundaries
 // is reversed once per span it depends on, each run adding that span's
 // derivatives (the field gradient, the same in every run, is gathered after
 // the last).
+// With `store` >= 0 the step's node values are already in that store (recomputed
+// ahead, adjoint_recompute).
+static mpa::AdjointStepArgs adjoint_args(const AdjTarget& t, const void* in, int64_t m, hipStream_t stream);
+
 static int adjoint_long_step(const AdjTarget& t, const void* in, const void* g_out, void* g_in, int64_t m,
-                             double* param_grad, hipStream_t stream) {
+                             double* param_grad, hipStream_t stream, int store = -1) {
     mpa_plan* p = t.p;
-    const int s = p->sched.span_of(m);
     const int M = p->prm.M, S = (int)p->beta2.size();
-    const double gain = p->sched.amp_after(m) ? p->lumped : 1.0;
-    // a boundary-crossing step's own node-scale row carries sigma_j; the reverse kernel
-    // takes sigma_j from the node weights and the row without it
-    const int ns_row = s < S ? gain_row(p, m, s) : plain_row(p, m);
-    mpa::AdjointStepArgs a;
-    a.in = in;
+    const int s = p->sched.span_of(m);
+    mpa::AdjointStepArgs a = adjoint_args(t, in, m, stream);
     a.g_out = g_out;
-    a.g_blk = t.w->gblk;
-    a.partial = (double*)t.w->partial;
-    a.node_store = t.w->node;
-    a.last_store = t.w->last;
-    a.n = p->prm.n;
-    a.block = p->block;
-    a.lead = p->halo + p->shift;
-    a.core = p->core;
-    a.n_blocks = p->n_blocks;
-    a.phase = (const char*)p->phase + (size_t)s * (M + 1) * p->block * p->elem;
-    a.phase_last = (const char*)p->phase_last + (size_t)s * p->block * 16;
-    a.node_scale = (const char*)p->node_scale + (size_t)ns_row * 2 * (M + 1) * (p->elem / 2);
-    a.twiddle = p->twiddle;
-    a.twiddle64 = p->twiddle64;
-    a.taper = p->taper;
-    a.M = M;
-    a.n_iter = p->prm.n_iter;
-    a.out_scale = p->row_out[ns_row] / p->block * gain;
-    a.w1 = 2.0 * 3.14159265358979323846 / (p->block * p->prm.dt);
-    a.precision = p->prm.precision;
-    a.batch = t.batch;
-    a.grid = t.grid;
-    a.stream = stream;
+    if (store >= 0) {
+        a.part = mpa::ADJ_REVERSE;
+        const size_t first = (size_t)store * t.n_items;
+        a.node_store = (char*)t.w->node + first * p->prm.n_iter * M * 3 * p->block * p->elem;
+        a.last_store = (char*)t.w->last + first * p->block * 16;
+    }
     mpa::AdjointGatherArgs g;
     g.g_blk = t.w->gblk;
     g.g_in = g_in;
@@ -1158,6 +1194,56 @@ static int adjoint_long_step(const AdjTarget& t, const void* in, const void* g_o
         e = mpa::launch_adjoint_gather(g);
         if (e != hipSuccess) return fail(MPA_EDEVICE, "adjoint gather launch failed: %s", hipGetErrorString(e));
     }
+    return MPA_OK;
+}
+
+static mpa::AdjointStepArgs adjoint_args(const AdjTarget& t, const void* in, int64_t m, hipStream_t stream) {
+    mpa_plan* p = t.p;
+    const int M = p->prm.M;
+    const double gain = p->sched.amp_after(m) ? p->lumped : 1.0;
+    const AdjRows rows = adjoint_rows(p, m);
+    const int s = rows.s, ns_row = rows.ns_row;
+    mpa::AdjointStepArgs a{};
+    a.part = mpa::ADJ_WHOLE;
+    a.steps = 1;
+    a.in_stride = t.count;
+    a.in = in;
+    a.g_blk = t.w->gblk;
+    a.partial = (double*)t.w->partial;
+    a.node_store = t.w->node;
+    a.last_store = t.w->last;
+    a.n = p->prm.n;
+    a.block = p->block;
+    a.lead = p->halo + p->shift;
+    a.core = p->core;
+    a.n_blocks = p->n_blocks;
+    a.phase = (const char*)p->phase + (size_t)s * (M + 1) * p->block * p->elem;
+    a.phase_last = (const char*)p->phase_last + (size_t)s * p->block * 16;
+    a.node_scale = (const char*)p->node_scale + (size_t)ns_row * 2 * (M + 1) * (p->elem / 2);
+    a.twiddle = p->twiddle;
+    a.twiddle64 = p->twiddle64;
+    a.taper = p->taper;
+    a.M = M;
+    a.n_iter = p->prm.n_iter;
+    a.out_scale = p->row_out[ns_row] / p->block * gain;
+    a.w1 = 2.0 * 3.14159265358979323846 / (p->block * p->prm.dt);
+    a.precision = p->prm.precision;
+    a.batch = t.batch;
+    a.grid = t.grid;
+    a.stream = stream;
+    return a;
+}
+
+// Forward recomputes of the `steps` long steps from m (inputs one after another
+// at `in`, same tables) into stores 0 .. steps - 1, in one launch.
+static int adjoint_recompute(const AdjTarget& t, const void* in, int64_t m, int steps, hipStream_t stream) {
+    mpa_plan* p = t.p;
+    mpa::AdjointStepArgs a = adjoint_args(t, in, m, stream);
+    a.part = mpa::ADJ_RECOMPUTE;
+    a.steps = steps;
+    a.node_w = (const char*)p->adj_nodew + (size_t)p->sched.span_of(m) * 3 * (p->prm.M + 1) * sizeof(double);
+    const hipError_t e = mpa::launch_adjoint_step(a);
+    if (e != hipSuccess) return fail(MPA_EDEVICE, "adjoint recompute launch failed: %s", hipGetErrorString(e));
     return MPA_OK;
 }
 
@@ -1239,6 +1325,31 @@ static int forward_checkpointed(const AdjTarget& t, void* field, double z0, doub
     return MPA_OK;
 }
 
+// Reverse of the `q` long steps from s0 (inputs in `slots`), last to first: the
+// gradient in *ga goes to *gb and back, *ga holding it at the end.  Runs of steps
+// with the same tables are recomputed ahead, w->ahead at a time.
+static int adjoint_steps(const AdjTarget& t, const void* slots, int64_t s0, int64_t q, void** ga, void** gb,
+                         double* param_grad, hipStream_t s) {
+    mpa_plan* p = t.p;
+    const int S = (int)p->beta2.size();
+    for (int64_t i = q - 1; i >= 0;) {
+        const AdjRows rows = adjoint_rows(p, s0 + i);
+        int64_t run = 1;
+        if (rows.s < S)                               // (a boundary-crossing step is reversed once per span)
+            while (run < t.w->ahead && run <= i && adjoint_rows(p, s0 + i - run) == rows) ++run;
+        const bool apart = run >= 4;
+        if (!apart) run = 1;
+        else if (int st = adjoint_recompute(t, field_at(t, slots, i - run + 1), s0 + i - run + 1, (int)run, s)) return st;
+        for (int64_t r = run - 1; r >= 0; --r, --i) {
+            const int st = adjoint_long_step(t, field_at(t, slots, i), *ga, *gb, s0 + i, param_grad, s,
+                                             apart ? (int)r : -1);
+            if (st) return st;
+            std::swap(*ga, *gb);
+        }
+    }
+    return MPA_OK;
+}
+
 // Reverse pass over [z0, z1] from the forward checkpoints (see mpa_adjoint).
 static int reverse(const AdjTarget& t, const void* checkpoints, void* grad, double z0, double z1,
                    double* param_grad, int64_t store_steps, hipStream_t s) {
@@ -1264,11 +1375,8 @@ static int reverse(const AdjTarget& t, const void* checkpoints, void* grad, doub
         void* gb = w->gb;
         if (mpa::launch_convert(grad, p->prm.precision, ga, MPA_C128, t.count, s) != hipSuccess)
             return fail(MPA_EDEVICE, "gradient conversion failed");
-        for (int64_t i = m1 - m0 - 1; i >= 0; --i) {
-            st = adjoint_long_step(t, field_at(t, w->inputs, i), ga, gb, m0 + i, param_grad, s);
-            if (st) return st;
-            std::swap(ga, gb);
-        }
+        st = adjoint_steps(t, w->inputs, m0, m1 - m0, &ga, &gb, param_grad, s);
+        if (st) return st;
         if (mpa::launch_convert(ga, MPA_C128, grad, p->prm.precision, t.count, s) != hipSuccess)
             return fail(MPA_EDEVICE, "gradient conversion failed");
         return MPA_OK;
@@ -1308,12 +1416,7 @@ static int reverse(const AdjTarget& t, const void* checkpoints, void* grad, doub
     const int64_t K = (int64_t)seg.size();
     auto seg_end = [&](int64_t k) { return k + 1 < K ? seg[k + 1] : m1; };
     auto reverse_steps = [&](const void* slots, int64_t s0, int64_t q) {
-        for (int64_t i = q - 1; i >= 0; --i) {
-            int rs = adjoint_long_step(t, field_at(t, slots, i), ga, gb, s0 + i, param_grad, s);
-            if (rs) return rs;
-            std::swap(ga, gb);
-        }
-        return (int)MPA_OK;
+        return adjoint_steps(t, slots, s0, q, &ga, &gb, param_grad, s);
     };
     if (overlap) {
         // Segment k's inputs live in half (K - 1 - k) % 2 of the slots.  The
