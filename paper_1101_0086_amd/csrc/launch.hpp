@@ -30,7 +30,7 @@ struct NodeBuffers {
 // of every instance of a batch.
 struct BlockStepArgs {
     const void* in;          // field at z0 (N complex of the plan's precision)
-    void* out;               // field at z0 + L (must not alias `in`)
+    void* out;               // field at z0 + L (may be `in` for one block, else must not alias it)
     int64_t n;
     int32_t block;
     int32_t lead;            // samples of each window before its core: halo + window shift
@@ -48,6 +48,9 @@ struct BlockStepArgs {
     const BatchItems* batch; // nullptr for a single field
     const NodeBuffers* nodes;// node-parallel schedule (single field); nullptr: fused wavefront kernel
     hipStream_t stream;
+    // node-parallel march of one full window: psi_0 of this step is in place (the step
+    // before computed it); compute the next step's psi_0 at the end
+    bool psi0_ready = false, next_psi0 = false;
 };
 
 bool block_step_supported(int precision, int block, int n_iter);

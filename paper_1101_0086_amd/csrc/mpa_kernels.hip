@@ -67,7 +67,8 @@ struct StepTables {
         __syncthreads();                                                               \
     }
 
-// One field: one workgroup per block.  Bound by the instructions of its 19
+// One field: one workgroup per block (`out` may be `in` when there is one block:
+// every read of it precedes the workgroup's first transform).  Bound by the instructions of its 19
 // dependent transforms (M = 4, two sweeps) and the exchange latency that two
 // waves per SIMD leave open.  2^22 modes, 2048 blocks of 4096, 8 long steps:
 // 2.62 ms with 8-point DFTs behind seven twiddle products and the last node
@@ -81,7 +82,7 @@ struct StepTables {
 // otherwise take up to 512 and keep one workgroup per CU.
 template <typename T, int B, int NIT>
 __global__ void __launch_bounds__(B / PTS) __attribute__((amdgpu_waves_per_eu(2)))
-mpa_block_kernel(const cx<T>* __restrict__ in, cx<T>* __restrict__ out, long long n, int core,
+mpa_block_kernel(const cx<T>* in, cx<T>* out, long long n, int core,
                  int lead, const cx<T>* __restrict__ phase, const cx<double>* __restrict__ phase_last,
                  const T* __restrict__ node_scale, const cx<T>* __restrict__ tw,
                  const cx<double>* __restrict__ tw64, const double* __restrict__ taper, int M, T sigma,

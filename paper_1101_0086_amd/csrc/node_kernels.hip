@@ -9,7 +9,8 @@
 //           psi^(s)_l (psi^(0)_l = psi_0), storing U^(s)_l; in sweep 0 one more
 //           per block computes U_0 / 2 = i sigma dz F[|A_0|^2 A_0] / 2, which
 //           only the sums need (many blocks: init does)
-//   final   one workgroup per block: step 7 from psi^(n_iter)_M, scatter of the core.
+//   final   one workgroup per block: step 7 from psi^(n_iter)_M, scatter of the core
+//           (a march of one full window: and the next step's init).
 // psi^(s+1)_l = psi_0 + U_0/2 + sum_{0<j<l} U_j + U_l/2 (Eq. 6, FP64, left to
 // right) is added up by the workgroup that needs it (NP_OWN), or, where those
 // sums are long and CUs idle, by a launch of its own after each sweep, one
@@ -226,13 +227,16 @@ np_sum_kernel(cx<double>* __restrict__ psi0_buf, const cx<T>* __restrict__ h0_bu
     }
 }
 
-// OWN: psi^(n_iter)_M from the last sweep's increments u_buf, else in psi0_buf (np_sum_kernel)
-template <typename T, int B, bool OWN, bool FEW>
+// OWN: psi^(n_iter)_M from the last sweep's increments u_buf, else in psi0_buf (np_sum_kernel).
+// NEXT (one full window): the stored field is the next long step's input, so the workgroup
+// goes on to its psi_0, as np_init_kernel computes it (4096 points, FP64, M = 16, three
+// sweeps: 52 to 51 us a long step; a launch and its first loads).
+template <typename T, int B, bool OWN, bool FEW, bool NEXT>
 __global__ void __launch_bounds__(B / PTS)
-np_final_kernel(const cx<double>* __restrict__ psi0_buf, const cx<T>* __restrict__ h0_buf,
+np_final_kernel(cx<double>* __restrict__ psi0_buf, const cx<T>* __restrict__ h0_buf,
                 const cx<T>* __restrict__ u_buf, cx<T>* __restrict__ out, long long n, int core, int lead,
-                const cx<double>* __restrict__ phase_last, const cx<double>* __restrict__ tw64, int M,
-                double out_scale) {
+                const cx<double>* __restrict__ phase_last, const cx<double>* __restrict__ tw64,
+                const double* __restrict__ taper, int M, double out_scale) {
     constexpr int R = PTS;
     constexpr int NT = B / R;
     __shared__ cx<double> lds64[(FEW ? 2 : 1) * B];
@@ -259,6 +263,12 @@ np_final_kernel(const cx<double>* __restrict__ psi0_buf, const cx<T>* __restrict
     for (int m = 0; m < R; ++m) {
         const int t = tid + NT * m;
         if (t >= lead && t < lead + clen) out[c0 + (t - lead)] = narrow<T>(v[m]);
+        if constexpr (NEXT) v[m] = scale(widen(narrow<T>(v[m])), taper[t]);
+    }
+    if constexpr (NEXT) {
+        block_fft<double, B, +1, FEW, TW_AHEAD>(v, e0, e1, tw64, tid);
+#pragma unroll
+        for (int m = 0; m < R; ++m) psi0_buf[base + tid + NT * m] = v[m];
     }
 }
 
@@ -304,8 +314,10 @@ static hipError_t node_step_typed(const BlockStepArgs& a) {
                            static_cast<const T*>(a.node_scale), static_cast<const cx<T>*>(a.twiddle), tw64,
                            static_cast<const double*>(a.taper), T(a.sigma));
     };
-    if (few) init(np_init_kernel<T, B, true>);
-    else init(np_init_kernel<T, B, false>);
+    if (!a.psi0_ready) {
+        if (few) init(np_init_kernel<T, B, true>);
+        else init(np_init_kernel<T, B, false>);
+    }
     const long long total = (long long)a.n_blocks * B;
     const dim3 sum_groups((unsigned)((total + SUM_TPB - 1) / SUM_TPB));
     const bool dbuf = (long long)a.n_blocks * (a.M + 1) <= NODE_DBUF_GROUPS;
@@ -334,12 +346,20 @@ static hipError_t node_step_typed(const BlockStepArgs& a) {
     const auto final = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3(a.n_blocks), threads, 0, a.stream, psi0, h0,
                            static_cast<const cx<T>*>(nb.u[(a.n_iter - 1) & 1]), static_cast<cx<T>*>(a.out),
-                           (long long)a.n, a.core, a.lead, static_cast<const cx<double>*>(a.phase_last), tw64, a.M,
-                           a.out_scale);
+                           (long long)a.n, a.core, a.lead, static_cast<const cx<double>*>(a.phase_last), tw64,
+                           static_cast<const double*>(a.taper), a.M, a.out_scale);
     };
-    if (apart) final(np_final_kernel<T, B, false, true>);
-    else if (few) final(np_final_kernel<T, B, true, true>);
-    else final(np_final_kernel<T, B, true, false>);
+    if (a.next_psi0) {
+        if (a.n_blocks != 1 || a.n != B || a.lead != 0) return hipErrorInvalidValue;
+        if (apart) final(np_final_kernel<T, B, false, true, true>);
+        else final(np_final_kernel<T, B, true, true, true>);
+    } else if (apart) {
+        final(np_final_kernel<T, B, false, true, false>);
+    } else if (few) {
+        final(np_final_kernel<T, B, true, true, false>);
+    } else {
+        final(np_final_kernel<T, B, true, false, false>);
+    }
     return hipGetLastError();
 }
 
