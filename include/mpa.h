@@ -100,8 +100,8 @@ typedef enum {
  *     node of a sweep independent): n_iter + 2 launches per long step (and
  *     n_iter more for long trapezoid sums), the node work of a sweep as
  *     n_blocks x M workgroups, psi_0 and the increments of two sweeps kept in
- *     device memory (plan-owned,
- *     n_blocks x (2 M + 1) x B complex plus n_blocks x B FP64 complex).   */
+ *     device memory (plan-owned, n_blocks x (2 M + 1) x B complex plus
+ *     n_blocks x B FP64 complex).                                           */
 typedef enum {
     MPA_WAVEFRONT = 0,
     MPA_NODE_PARALLEL = 1
@@ -359,7 +359,7 @@ int mpa_batch_propagate(mpa_batch_plan* plan, void* fields, double z0, double z1
  * kernels run the same per-block operations, with the work items walked by a
  * fixed grid of workgroups.  The workspace (held by the batch plan) is
  * grid x (3 n_iter M + 1) x block (few work items: as mpa_adjoint's) +
- * work_items x block complex samples plus the kept step inputs.                                                     */
+ * work_items x block complex samples plus the kept step inputs.             */
 int mpa_batch_checkpoint_count(const mpa_batch_plan* plan, double z0, double z1, int64_t* count);
 int mpa_batch_propagate_checkpointed(mpa_batch_plan* plan, void* fields, double z0, double z1,
                                      void* checkpoints, void* stream);

@@ -68,9 +68,9 @@ struct StepTables {
     }
 
 // One field: one workgroup per block (`out` may be `in` when there is one block:
-// every read of it precedes the workgroup's first transform).  Bound by the instructions of its 19
-// dependent transforms (M = 4, two sweeps) and the exchange latency that two
-// waves per SIMD leave open.  2^22 modes, 2048 blocks of 4096, 8 long steps:
+// every read of it precedes the workgroup's first transform).  Bound by the
+// instructions of its 19 dependent transforms (M = 4, two sweeps) and the
+// exchange latency that two waves per SIMD leave open.  2^22 modes, 2048 blocks of 4096, 8 long steps:
 // 2.62 ms with 8-point DFTs behind seven twiddle products and the last node
 // selected per element, 2.29 ms with the passes of block_fft.hpp, the last
 // node behind a uniform branch and the node's two scales folded (1446 against
@@ -87,7 +87,7 @@ mpa_block_kernel(const cx<T>* in, cx<T>* out, long long n, int core,
                  const T* __restrict__ node_scale, const cx<T>* __restrict__ tw,
                  const cx<double>* __restrict__ tw64, const double* __restrict__ taper, int M, T sigma,
                  double out_scale) {
-    // two FP64 exchange buffers (FP32 node transforms use the first)
+    // two FP64 exchange buffers (a pair of FP32 node transforms uses both, one alone the first)
     __shared__ cx<double> lds64[2 * B];
     LDS_TWIDDLES(T, B)
     const long long c0 = (long long)blockIdx.x * core;
