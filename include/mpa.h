@@ -86,9 +86,8 @@ typedef enum {
     MPA_C128 = 1    /* FP64 everywhere                                        */
 } mpa_precision;
 
-/* Order in which a block's node evaluations run; both give the same field
- * (bitwise for MPA_C64; for MPA_C128 to the last bits, max relative
- * difference of order 1e-16).
+/* Order in which a block's node evaluations run; both give bitwise the same
+ * field.
  *   MPA_WAVEFRONT: one fused kernel per long step, one workgroup per block;
  *     nodes l = 1..M in turn and, at each node, all n_iter sweeps (sweep n+1
  *     at node l needs only sweep-n values at nodes <= l), with psi_0 and
@@ -357,7 +356,9 @@ int mpa_batch_propagate(mpa_batch_plan* plan, void* fields, double z0, double z1
  * dl/dsigma is weighted by that scale.  Each instance's G(A(z0)) is that of
  * mpa_adjoint on a plan of its own (sigma scaled, same parameters): the
  * kernels run the same per-block operations, with the work items walked by a
- * fixed grid of workgroups.  The workspace (held by the batch plan) is
+ * fixed grid of workgroups, and its field after a march is likewise that of
+ * mpa_propagate (bitwise, whichever kernels the plan of its own runs on).
+ * The workspace (held by the batch plan) is
  * grid x (3 n_iter M + 1) x block (few work items: as mpa_adjoint's) +
  * work_items x block complex samples plus the kept step inputs.             */
 int mpa_batch_checkpoint_count(const mpa_batch_plan* plan, double z0, double z1, int64_t* count);

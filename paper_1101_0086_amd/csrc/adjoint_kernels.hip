@@ -73,6 +73,19 @@ __device__ __forceinline__ void node_fft(cx<T> (&v)[PTS], cx<T>*& db0, cx<T>*& d
     }
 }
 
+// ... of v_m f_m (F: one factor a point, or the same at all)
+template <typename T, int B, int SG, bool DB, typename F>
+__device__ __forceinline__ void node_fft_scaled(cx<T> (&v)[PTS], const F& f, cx<T>*& db0, cx<T>*& db1, cx<T>* lds,
+                                                const cx<T>* __restrict__ tw, const cx<T>* twl, int tid) {
+    if constexpr (DB) {
+        block_fft_scaled<T, B, SG, true, TW_PRODUCTS, true>(v, f, db0, db1, tw, tid, nullptr, twl);
+    } else {
+        cx<T>* l0 = lds;
+        cx<T>* l1 = lds;
+        block_fft_scaled<T, B, SG, false, TW_PRODUCTS, true>(v, f, l0, l1, tw, tid, nullptr, twl);
+    }
+}
+
 }  // namespace
 
 // The two halves of a reverse step, in one launch or apart (AdjointPart in

@@ -96,13 +96,58 @@ __device__ __forceinline__ void dft4(cx<T>& x0, cx<T>& x1, cx<T>& x2, cx<T>& x3)
     x3 = t1 - t3;
 }
 
+// The same of x_q f_q.  The product of the second input of each first
+// butterfly is rounded, the first one's is fused into the sum and the
+// difference, by the source and not as the compiler happens to (which fused
+// it for one kernel's inputs and not for another's: schedules that are to
+// agree bitwise did not in FP64).
+template <typename T>
+__device__ __forceinline__ void dft2_scaled(cx<T>& a, cx<T>& b, T fa, T fb) {
+    const cx<T> p = scale(b, fb), t = a;
+    a = mad(t, fa, p);
+    b = {fma(t.re, fa, -p.re), fma(t.im, fa, -p.im)};
+}
+
+// the second level of dft4, of first-level sums and differences t0 = x0 + x2, t1 = x0 - x2,
+// t2 = x1 + x3, t3 = x1 - x3
+template <int SIGN, typename T>
+__device__ __forceinline__ void dft4_second(cx<T>& t0, cx<T>& t2, cx<T>& t1, cx<T>& t3) {
+    const cx<T> a = t0, b = t2, c = t1, d = rot<SIGN>(t3);
+    t0 = a + b;
+    t1 = a - b;
+    t2 = c + d;
+    t3 = c - d;
+}
+
+template <int SIGN, typename T>
+__device__ __forceinline__ void dft4_scaled(cx<T>& x0, cx<T>& x1, cx<T>& x2, cx<T>& x3, T f0, T f1, T f2, T f3) {
+    dft2_scaled(x0, x2, f0, f2);
+    dft2_scaled(x1, x3, f1, f3);
+    dft4_second<SIGN>(x0, x1, x2, x3);
+}
+
+template <int SIGN, typename T>
+__device__ __forceinline__ void dft8_last(cx<T> (&x)[8]);
+
 // 8-point DFT as two 4-point DFTs of the even and odd samples:
 // X_k = E_k + w^k O_k, X_{k+4} = E_k - w^k O_k, w = exp(SIGN 2 pi i / 8).
 template <int SIGN, typename T>
 __device__ __forceinline__ void dft8(cx<T> (&x)[8]) {
-    const T h = T(0.70710678118654752440084436210484903928);
     dft4<SIGN>(x[0], x[2], x[4], x[6]);
     dft4<SIGN>(x[1], x[3], x[5], x[7]);
+    dft8_last<SIGN>(x);
+}
+
+template <int SIGN, typename T>
+__device__ __forceinline__ void dft8_scaled(cx<T> (&x)[8], const T (&f)[8]) {
+    dft4_scaled<SIGN>(x[0], x[2], x[4], x[6], f[0], f[2], f[4], f[6]);
+    dft4_scaled<SIGN>(x[1], x[3], x[5], x[7], f[1], f[3], f[5], f[7]);
+    dft8_last<SIGN>(x);
+}
+
+template <int SIGN, typename T>
+__device__ __forceinline__ void dft8_last(cx<T> (&x)[8]) {
+    const T h = T(0.70710678118654752440084436210484903928);
     // twiddle the odd half: O_1 *= w, O_2 *= w^2 = SIGN i, O_3 *= w^3
     // w O_1 = h (O_1 + SIGN i O_1) and w^3 O_3 = h (-O_3 + SIGN i O_3): the sums
     // are exact up to one rounding, the factor h is applied inside an
@@ -132,6 +177,18 @@ __device__ __forceinline__ void dft(cx<T> (&x)[r]) {
     } else {
         static_assert(r == 8, "radix");
         dft8<SIGN>(x);
+    }
+}
+
+template <int SIGN, int r, typename T>
+__device__ __forceinline__ void dft_scaled(cx<T> (&x)[r], const T (&f)[r]) {
+    if constexpr (r == 2) {
+        dft2_scaled(x[0], x[1], f[0], f[1]);
+    } else if constexpr (r == 4) {
+        dft4_scaled<SIGN>(x[0], x[1], x[2], x[3], f[0], f[1], f[2], f[3]);
+    } else {
+        static_assert(r == 8, "radix");
+        dft8_scaled<SIGN>(x, f);
     }
 }
 
@@ -325,9 +382,9 @@ __device__ __forceinline__ void pass_write(const cx<T> (&v)[8], cx<T>* out, int 
     for (int q = 0; q < 8; ++q) lds_at<T>(out, a, q * p) = v[q];
 }
 
-// the first pass: no twiddles, 8 / r butterflies of radix r
-template <typename T, int B, int SIGN, bool LEAN>
-__device__ __forceinline__ void pass_first(const cx<T> (&v)[8], cx<T>* out, int tid) {
+// the first pass: no twiddles, 8 / r butterflies of radix r; SC: of v_m f_m
+template <typename T, int B, int SIGN, bool LEAN, bool SC = false>
+__device__ __forceinline__ void pass_first(const cx<T> (&v)[8], cx<T>* out, int tid, const T* f = nullptr) {
     constexpr int NT = B / 8, r = first_radix(B), NB = 8 / r;
     const int a = lds_base<T, LEAN>(tid * r);
 #pragma unroll
@@ -335,15 +392,22 @@ __device__ __forceinline__ void pass_first(const cx<T> (&v)[8], cx<T>* out, int 
         cx<T> x[r];
 #pragma unroll
         for (int q = 0; q < r; ++q) x[q] = v[u + q * NB];
-        dft<SIGN, r>(x);
+        if constexpr (SC) {
+            T fx[r];
+#pragma unroll
+            for (int q = 0; q < r; ++q) fx[q] = f[u + q * NB];
+            dft_scaled<SIGN, r>(x, fx);
+        } else {
+            dft<SIGN, r>(x);
+        }
 #pragma unroll
         for (int q = 0; q < r; ++q) lds_at<T>(out, a, u * NT * r + q) = x[q];
     }
 }
 
-template <typename T, int B, int SIGN, int S, int NP, bool DBUF, int TWS, bool LEAN, bool EXACT8>
+template <typename T, int B, int SIGN, int S, int NP, bool DBUF, int TWS, bool LEAN, bool EXACT8, bool SC>
 __device__ __forceinline__ void passes(cx<T> (&v)[8], cx<T>* buf0, cx<T>* buf1, PassTw<T> (&wall)[NP - 1],
-                                       const cx<T>* __restrict__ tw, const cx<T>* tl, int tid) {
+                                       const cx<T>* __restrict__ tw, const cx<T>* tl, int tid, const T* f) {
     if constexpr (TWS == TW_AHEAD) {
         int t = tid;
         asm volatile("" : "+v"(t));          // loaded here, not earlier
@@ -357,7 +421,7 @@ __device__ __forceinline__ void passes(cx<T> (&v)[8], cx<T>* buf0, cx<T>* buf1, 
     cx<T>* in = DBUF ? ((S % 2) ? buf0 : buf1) : buf0;
     cx<T>* out = DBUF ? ((S % 2) ? buf1 : buf0) : buf0;
     if constexpr (first) {
-        pass_first<T, B, SIGN, LEAN>(v, out, tid);
+        pass_first<T, B, SIGN, LEAN, SC>(v, out, tid, f);
     } else {
         __syncthreads();        // the previous pass's writes are visible
         pass_read<T, B, LEAN>(v, in, tid);
@@ -400,7 +464,7 @@ __device__ __forceinline__ void passes(cx<T> (&v)[8], cx<T>* buf0, cx<T>* buf1, 
         else dft8_tw<SIGN>(v, w);
         if constexpr (!last) pass_write<T, B, S, LEAN>(v, out, tid);
     }
-    if constexpr (!last) passes<T, B, SIGN, S + 1, NP, DBUF, TWS, LEAN, EXACT8>(v, buf0, buf1, wall, tw, tl, tid);
+    if constexpr (!last) passes<T, B, SIGN, S + 1, NP, DBUF, TWS, LEAN, EXACT8, SC>(v, buf0, buf1, wall, tw, tl, tid, f);
 }
 
 // B-point transform of the workgroup's registers (see the file comment); must
@@ -418,9 +482,11 @@ __device__ __forceinline__ void passes(cx<T> (&v)[8], cx<T>* buf0, cx<T>* buf1, 
 // `tw` holds exp(+2 pi i j / B), j = 0..B-1; `regs` for TW_REGS, `tl` for
 // TW_TABLE and TW_PRODUCTS.  LEAN: every access forms its LDS address (one operation) instead of
 // the caller's loop keeping it in a register, for callers that spill otherwise.
-template <typename T, int B, int SIGN, bool DBUF, int TWS, bool LEAN = false, bool EXACT8 = sizeof(T) == 4>
+template <typename T, int B, int SIGN, bool DBUF, int TWS, bool LEAN = false, bool EXACT8 = sizeof(T) == 4,
+          bool SC = false>
 __device__ __forceinline__ void block_fft(cx<T> (&v)[8], cx<T>*& buf0, cx<T>*& buf1, const cx<T>* __restrict__ tw,
-                                          int tid, const Twiddles<T, B>* regs = nullptr, const cx<T>* tl = nullptr) {
+                                          int tid, const Twiddles<T, B>* regs = nullptr, const cx<T>* tl = nullptr,
+                                          const T* f = nullptr) {
     static_assert((B & (B - 1)) == 0 && B >= 64, "power-of-two block of at least 64 points");
     constexpr int NP = n_passes(B);
     PassTw<T> w[NP - 1];
@@ -428,7 +494,7 @@ __device__ __forceinline__ void block_fft(cx<T> (&v)[8], cx<T>*& buf0, cx<T>*& b
 #pragma unroll
         for (int i = 0; i < NP - 1; ++i) w[i] = regs->w[i];
     }
-    passes<T, B, SIGN, 0, NP, DBUF, TWS, LEAN, EXACT8>(v, buf0, buf1, w, tw, tl, tid);
+    passes<T, B, SIGN, 0, NP, DBUF, TWS, LEAN, EXACT8, SC>(v, buf0, buf1, w, tw, tl, tid, f);
     if constexpr (DBUF && (NP - 1) % 2 == 1) {
         cx<T>* s = buf0;
         buf0 = buf1;
@@ -436,21 +502,39 @@ __device__ __forceinline__ void block_fft(cx<T> (&v)[8], cx<T>*& buf0, cx<T>*& b
     }
 }
 
+// The transform of v_m f_m (f real, one factor a point): half of the products
+// are fused into the first pass's additions (dft2_scaled).
+template <typename T, int B, int SIGN, bool DBUF, int TWS, bool LEAN = false, bool EXACT8 = sizeof(T) == 4>
+__device__ __forceinline__ void block_fft_scaled(cx<T> (&v)[8], const T (&f)[8], cx<T>*& buf0, cx<T>*& buf1,
+                                                 const cx<T>* __restrict__ tw, int tid,
+                                                 const Twiddles<T, B>* regs = nullptr, const cx<T>* tl = nullptr) {
+    block_fft<T, B, SIGN, DBUF, TWS, LEAN, EXACT8, true>(v, buf0, buf1, tw, tid, regs, tl, f);
+}
+
+// ... with the same factor at every point
+template <typename T, int B, int SIGN, bool DBUF, int TWS, bool LEAN = false, bool EXACT8 = sizeof(T) == 4>
+__device__ __forceinline__ void block_fft_scaled(cx<T> (&v)[8], T s, cx<T>*& buf0, cx<T>*& buf1,
+                                                 const cx<T>* __restrict__ tw, int tid,
+                                                 const Twiddles<T, B>* regs = nullptr, const cx<T>* tl = nullptr) {
+    const T f[8] = {s, s, s, s, s, s, s, s};
+    block_fft<T, B, SIGN, DBUF, TWS, LEAN, EXACT8, true>(v, buf0, buf1, tw, tid, regs, tl, f);
+}
+
 // ---- two transforms side by side --------------------------------------------------
 // Two independent B-point transforms of one workgroup, pass by pass with one
 // barrier for both, each between two buffers of its own (as DBUF): the second
 // one's reads are in flight under the first one's butterflies, and the first
 // one's writes under the second's.
-template <typename T, int B, int SA, int SB, int S, int NP>
+template <typename T, int B, int SA, int SB, int S, int NP, bool SC>
 __device__ __forceinline__ void pair_passes(cx<T> (&va)[8], cx<T> (&vb)[8], cx<T>* a0, cx<T>* a1, cx<T>* b0, cx<T>* b1,
-                                            const PassTw<T> (&w)[NP - 1], int tid) {
+                                            const PassTw<T> (&w)[NP - 1], int tid, const T* fa, const T* fb) {
     constexpr bool last = (S == NP - 1);
     // at 4096 points the reads share one address: the separate ones spill (272 against
     // 265 us a long step at 2^22 modes; 13.5 against 13.7 at 2^15, 1024 points)
     constexpr bool SHARED = B >= 4096;
     if constexpr (S == 0) {
-        pass_first<T, B, SA, false>(va, a0, tid);
-        pass_first<T, B, SB, false>(vb, b0, tid);
+        pass_first<T, B, SA, false, SC>(va, a0, tid, fa);
+        pass_first<T, B, SB, false, SC>(vb, b0, tid, fb);
     } else {
         __syncthreads();
         pass_read<T, B, SHARED>(va, (S % 2) ? a0 : a1, tid);
@@ -460,15 +544,17 @@ __device__ __forceinline__ void pair_passes(cx<T> (&va)[8], cx<T> (&vb)[8], cx<T
         dft8_tw<SB>(vb, w[S - 1]);
         if constexpr (!last) pass_write<T, B, S, false>(vb, (S % 2) ? b1 : b0, tid);
     }
-    if constexpr (!last) pair_passes<T, B, SA, SB, S + 1, NP>(va, vb, a0, a1, b0, b1, w, tid);
+    if constexpr (!last) pair_passes<T, B, SA, SB, S + 1, NP, SC>(va, vb, a0, a1, b0, b1, w, tid, fa, fb);
 }
 
-// The buffers of both are swapped on return as block_fft's are.
-template <typename T, int B, int SA, int SB>
+// The buffers of both are swapped on return as block_fft's are.  SC: the
+// transforms of va_m fa_m and vb_m fb_m, as block_fft_scaled.
+template <typename T, int B, int SA, int SB, bool SC = false>
 __device__ __forceinline__ void block_fft_pair(cx<T> (&va)[8], cx<T> (&vb)[8], cx<T>*& a0, cx<T>*& a1, cx<T>*& b0,
-                                               cx<T>*& b1, const Twiddles<T, B>& regs, int tid) {
+                                               cx<T>*& b1, const Twiddles<T, B>& regs, int tid, const T* fa = nullptr,
+                                               const T* fb = nullptr) {
     constexpr int NP = n_passes(B);
-    pair_passes<T, B, SA, SB, 0, NP>(va, vb, a0, a1, b0, b1, regs.w, tid);
+    pair_passes<T, B, SA, SB, 0, NP, SC>(va, vb, a0, a1, b0, b1, regs.w, tid, fa, fb);
     if constexpr ((NP - 1) % 2 == 1) {
         cx<T>* s = a0;
         a0 = a1;

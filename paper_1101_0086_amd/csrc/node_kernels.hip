@@ -16,10 +16,10 @@
 // sums are long and CUs idle, by a launch of its own after each sweep, one
 // thread per (block, frequency) (NP_SUMMED; see sums_apart).
 // Every operation, and the order of every sum, is that of the fused
-// wavefront kernel, so both schedules give the same field (bitwise for FP32
-// node evaluations; to the last bits in FP64, where the compiler fuses a few
-// products into additions differently in the two kernels); this one
-// exposes M times more workgroups for the node work, at the price of keeping
+// wavefront kernel, so both schedules give bitwise the same field (which
+// products are fused into additions is written out, see cx.hpp and
+// dft2_scaled; left to the compiler it differed between the two in FP64);
+// this one exposes M times more workgroups for the node work, at the price of keeping
 // psi_0, the increments and the nodes' spectra in device memory (L2/MALL-
 // resident at the sizes used here) instead of registers.
 //
@@ -115,7 +115,7 @@ __device__ __forceinline__ void trapezoid(cx<double> (&v)[PTS], const cx<double>
 #pragma unroll
     for (int m = 0; m < PTS; ++m) {
         const int t = tid + NT * m;
-        v[m] = psi0[t] + (v[m] + scale(widen(u[(size_t)(l - 1) * B + t]), 0.5));
+        v[m] = psi0[t] + mad(widen(u[(size_t)(l - 1) * B + t]), 0.5, v[m]);
     }
 }
 
@@ -184,10 +184,11 @@ np_node_kernel(const cx<T>* __restrict__ in, const cx<double>* __restrict__ psi0
     for (int m = 0; m < R; ++m) cur[m] = cmul(cur[m], ph[m]);
     __syncthreads();                              // the twiddle table is complete
     block_fft<T, B, -1, DBUF, TW_TABLE>(cur, l0, l1, tw, tid, nullptr, twl);
+    T f[R];
 #pragma unroll
-    for (int m = 0; m < R; ++m) cur[m] = cube(cur[m], c3);
+    for (int m = 0; m < R; ++m) f[m] = cube_factor(cur[m], c3);
     // step 4: U_l = i sigma dz e^{-Gamma_l} e^{-i beta_l} F[|A|^2 A]
-    block_fft<T, B, +1, DBUF, TW_TABLE>(cur, l0, l1, tw, tid, nullptr, twl);
+    block_fft_scaled<T, B, +1, DBUF, TW_TABLE>(cur, f, l0, l1, tw, tid, nullptr, twl);
 #pragma unroll
     for (int m = 0; m < R; ++m) u_buf[row + tid + NT * m] = rot<+1>(cmulc(cur[m], ph[m]));
 }
@@ -218,7 +219,7 @@ np_sum_kernel(cx<double>* __restrict__ psi0_buf, const cx<T>* __restrict__ h0_bu
             const cx<double> ud = widen(u[q]);
             const bool last = j0 + q == M - 1;
             if (!LAST || last) {
-                const cx<double> nxt = psi0 + (S + scale(ud, 0.5));
+                const cx<double> nxt = psi0 + mad(ud, 0.5, S);
                 if constexpr (LAST) psi0_buf[i] = nxt;
                 else psi_buf[row + (size_t)(j0 + q) * B] = narrow<T>(nxt);
             }
@@ -252,10 +253,10 @@ np_final_kernel(cx<double>* __restrict__ psi0_buf, const cx<T>* __restrict__ h0_
     }
     // step 7: A(z0 + L) = e^{Gamma_M} F^-1[psi_M e^{i beta_M}] (times the roll-off and gain)
 #pragma unroll
-    for (int m = 0; m < R; ++m) v[m] = scale(cmul(v[m], phase_last[tid + NT * m]), out_scale);
+    for (int m = 0; m < R; ++m) v[m] = cmul(v[m], phase_last[tid + NT * m]);
     cx<double>* e0 = lds64;
     cx<double>* e1 = lds64 + (FEW ? B : 0);
-    block_fft<double, B, -1, FEW, TW_AHEAD>(v, e0, e1, tw64, tid);
+    block_fft_scaled<double, B, -1, FEW, TW_AHEAD>(v, out_scale, e0, e1, tw64, tid);
     const long long c0 = (long long)b * core;
     const long long rest = n - c0;
     const int clen = rest < core ? (int)rest : core;

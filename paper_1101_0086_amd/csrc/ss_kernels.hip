@@ -47,19 +47,19 @@ ss_run_small_kernel(cx<ST>* __restrict__ field, const cx<double>* __restrict__ h
     // L dz/2
     block_fft<double, B, +1, true, TW_REGS>(v, l0, l1, tw, tid, &rt);
 #pragma unroll
-    for (int m = 0; m < R; ++m) v[m] = scale(cmul(v[m], half_ph[tid + NT * m]), half_scale);
-    block_fft<double, B, -1, true, TW_REGS>(v, l0, l1, tw, tid, &rt);
+    for (int m = 0; m < R; ++m) v[m] = cmul(v[m], half_ph[tid + NT * m]);
+    block_fft_scaled<double, B, -1, true, TW_REGS>(v, half_scale, l0, l1, tw, tid, &rt);
     for (int j = 1; j <= steps; ++j) {
         kick(v, sdz);
         block_fft<double, B, +1, true, TW_REGS>(v, l0, l1, tw, tid, &rt);
         if (j < steps) {
 #pragma unroll
-            for (int m = 0; m < R; ++m) v[m] = scale(cmul(v[m], fp[m]), full_scale);
+            for (int m = 0; m < R; ++m) v[m] = cmul(v[m], fp[m]);
         } else {
 #pragma unroll
-            for (int m = 0; m < R; ++m) v[m] = scale(cmul(v[m], half_ph[tid + NT * m]), end_scale);
+            for (int m = 0; m < R; ++m) v[m] = cmul(v[m], half_ph[tid + NT * m]);
         }
-        block_fft<double, B, -1, true, TW_REGS>(v, l0, l1, tw, tid, &rt);
+        block_fft_scaled<double, B, -1, true, TW_REGS>(v, j < steps ? full_scale : end_scale, l0, l1, tw, tid, &rt);
     }
 #pragma unroll
     for (int m = 0; m < R; ++m) field[tid + NT * m] = cx<ST>{ST(v[m].re), ST(v[m].im)};

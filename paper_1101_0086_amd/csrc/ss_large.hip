@@ -65,7 +65,12 @@ ss_rows_kernel(cx<ST>* __restrict__ y, int n1, const cx<double>* __restrict__ tw
     cx<double>* b1 = b0;
     block_fft<double, N2, +1, false, TW_AHEAD>(v, b0, b1, tw2, t);
 #pragma unroll
-    for (int m = 0; m < R; ++m) v[m] = scale(cmul(v[m], prow[t + NT * m]), scl);
+    for (int m = 0; m < R; ++m) {
+        // not scale(): the compiler may fuse these products into the transform's additions
+        // (block_fft_scaled, which writes that out, 2375 against 2302 us for 32 steps of 2^22 modes)
+        const cx<double> y = cmul(v[m], prow[t + NT * m]);
+        v[m] = {y.re * scl, y.im * scl};
+    }
     block_fft<double, N2, -1, false, TW_AHEAD>(v, b0, b1, tw2, t);
     // w_N^{n2 k1} for n2 = t + NT m: w_N^{t k1} (w_N^{NT k1})^m, two table
     // lookups per thread instead of one per point

@@ -140,12 +140,18 @@ win_cols_kernel(const cx<TIN>* __restrict__ src, cx<TOUT>* __restrict__ dst, int
         }
     }
     if constexpr (MODE == WC_NODE || MODE == WC_INV) block_fft<TK, N1, -1, DBUF, TW_AHEAD, false, true>(v, my, my1, tw1, t);
-    if constexpr (MODE == WC_NODE) {
-#pragma unroll
-        for (int m = 0; m < R; ++m) v[m] = cube(scale(v[m], cnode), dnode);
-    }
     if constexpr (MODE != WC_INV) {
-        block_fft<TK, N1, +1, DBUF, TW_AHEAD, false, true>(v, my, my1, tw1, t);
+        if constexpr (MODE == WC_NODE) {
+            TK f[R];
+#pragma unroll
+            for (int m = 0; m < R; ++m) {
+                v[m] = scale(v[m], cnode);
+                f[m] = cube_factor(v[m], dnode);
+            }
+            block_fft_scaled<TK, N1, +1, DBUF, TW_AHEAD, false, true>(v, f, my, my1, tw1, t);
+        } else {
+            block_fft<TK, N1, +1, DBUF, TW_AHEAD, false, true>(v, my, my1, tw1, t);
+        }
         Powers<TK> w(twl, twh, split, col, t, NT);
 #pragma unroll
         for (int m = 0; m < R; ++m) v[m] = cmul(v[m], w.next());
@@ -227,7 +233,7 @@ win_rows_kernel(WinRowArgs a, const cx<T>* __restrict__ tw2, const cx<double>* _
             const cx<double> u = widen(rot<+1>(cmulc(v[m], ph[NT * m])));
             const cx<double> s = a.first_node ? widen(u0[NT * m]) : S[NT * m];
             const cx<double> p0 = psi0[NT * m];
-            const cx<double> nxt = p0 + (s + scale(u, 0.5));
+            const cx<double> nxt = p0 + mad(u, 0.5, s);
             if constexpr (MODE == WR_LAST) {
                 z[m] = nxt;
             } else {
@@ -240,8 +246,8 @@ win_rows_kernel(WinRowArgs a, const cx<T>* __restrict__ tw2, const cx<double>* _
     if constexpr (MODE == WR_LAST) {
         const cx<double>* pl = static_cast<const cx<double>*>(a.ph_last) + base;
 #pragma unroll
-        for (int m = 0; m < R; ++m) z[m] = scale(cmul(z[m], pl[NT * m]), a.out_scale);
-        block_fft<double, N2, -1, false, TW_AHEAD, false, true>(z, d0, d1, tw2_64, t);
+        for (int m = 0; m < R; ++m) z[m] = cmul(z[m], pl[NT * m]);
+        block_fft_scaled<double, N2, -1, false, TW_AHEAD, false, true>(z, a.out_scale, d0, d1, tw2_64, t);
         cx<double>* dst = static_cast<cx<double>*>(a.dst) + woff + base;
         Powers<double> w(twl64, twh64, split, k1, t, NT);
 #pragma unroll
