@@ -50,7 +50,7 @@ ss_run_small_kernel(cx<ST>* __restrict__ field, const cx<double>* __restrict__ h
     for (int m = 0; m < R; ++m) v[m] = cmul(v[m], half_ph[tid + NT * m]);
     block_fft_scaled<double, B, -1, true, TW_REGS>(v, half_scale, l0, l1, tw, tid, &rt);
     for (int j = 1; j <= steps; ++j) {
-        kick(v, sdz);
+        kick<false>(v, sdz);
         block_fft<double, B, +1, true, TW_REGS>(v, l0, l1, tw, tid, &rt);
         if (j < steps) {
 #pragma unroll

@@ -105,7 +105,7 @@ ss_cols_kernel(cx<ST>* __restrict__ y, int n2, const cx<double>* __restrict__ tw
         block_fft<double, N1, -1, false, TW_AHEAD>(v, my, my1, tw1, t);   // x[N2 n1 + n2], n1 = t + NT m
     }
     if constexpr (MODE == SS_COL_MID) {
-        kick(v, sdz);
+        kick<true, (N1 >= 1024)>(v, sdz);
     }
     if constexpr (MODE != SS_COL_LAST) {
         block_fft<double, N1, +1, false, TW_AHEAD>(v, my, my1, tw1, t);   // Y[k1][n2], k1 = t + NT m
