@@ -25,11 +25,16 @@
 // of an 8-point DFT take 80 and seven.
 // Rounding, 4096 points, rms relative error against long double: 1.34e-7 in
 // FP32 (1.19e-7 with products of table twiddles), 2.7e-16 in FP64, 2.4e-16 with
-// EXACT8 (2.3e-16; 4.0e-16 with the seven twiddles formed from one table load).
+// W8_TABLE (2.3e-16; 4.0e-16 with the seven twiddles formed from one table load).
+// SEVEN takes 72 operations too, with seven stored twiddles: x_1, x_2, x_3 times
+// theirs, the first level's butterflies with w^4 .. w^7, two levels without: every
+// point meets one rounded twiddle a pass instead of three, 1.21e-7.
 //
 // SIGN = +1 is the transform with kernel exp(+i omega t) (the paper's F),
 // SIGN = -1 its unnormalised inverse.
 #pragma once
+
+#include <type_traits>
 
 #include "cx.hpp"
 
@@ -208,6 +213,24 @@ struct PassTw {
     cx<T> w1, w2, w4, w8;
 };
 
+// w .. w^7 (SEVEN)
+template <typename T>
+struct PassTw7 {
+    cx<T> w[7];
+};
+
+// Rounding of a transform (file comment):
+//   W8_FORMED  e^{i pi/4} w formed from w
+//   W8_TABLE   ... from the table
+//   SEVEN      w .. w^7, loaded from a pass table (pass_table in launch.hpp)
+enum Rounding { W8_FORMED = 0, W8_TABLE = 1, SEVEN = 2 };
+
+template <typename T>
+constexpr int rounding() { return sizeof(T) == 4 ? W8_TABLE : W8_FORMED; }
+
+template <typename T, int RND>
+using TwOf = std::conditional_t<RND == SEVEN, PassTw7<T>, PassTw<T>>;
+
 // 8-point DFT of x_q w^q (see the file comment), output in natural order.
 template <int SIGN, typename T>
 __device__ __forceinline__ void dft8_tw(cx<T> (&x)[8], const PassTw<T>& w) {
@@ -229,6 +252,24 @@ __device__ __forceinline__ void dft8_tw(cx<T> (&x)[8], const PassTw<T>& w) {
     x[3] = x3;
     x[4] = x4;
     x[6] = x6;
+}
+
+template <int SIGN, typename T>
+__device__ __forceinline__ void dft8_tw(cx<T> (&x)[8], const PassTw7<T>& t) {
+    const auto times = [](cx<T>& a, cx<T> w) {
+        if constexpr (SIGN < 0) w.im = -w.im;
+        a = cmul(a, w);
+    };
+    times(x[2], t.w[1]);
+    times(x[1], t.w[0]);
+    times(x[3], t.w[2]);
+    bfly<SIGN>(x[0], x[4], t.w[3]);
+    bfly<SIGN>(x[2], x[6], t.w[5]);
+    bfly<SIGN>(x[1], x[5], t.w[4]);
+    bfly<SIGN>(x[3], x[7], t.w[6]);
+    dft4_second<SIGN>(x[0], x[2], x[4], x[6]);
+    dft4_second<SIGN>(x[1], x[3], x[5], x[7]);
+    dft8_last<SIGN>(x);
 }
 
 // ---- passes --------------------------------------------------------------------
@@ -263,7 +304,7 @@ enum TwiddleSource { TW_REGS = 0, TW_AHEAD = 1, TW_PASS = 2, TW_TABLE = 3, TW_PR
 // e^{i pi/4} w: from the table in FP32, formed from w in FP64 (three 16-byte
 // loads per pass instead of four, 4 % of a 2^22-mode split-step, and an LDS
 // table that fits beside two 4096-point exchange buffers), or from the table
-// there too where the caller asks for it (EXACT8).
+// there too where the caller asks for it (W8_TABLE).
 template <typename T>
 constexpr int tl_rows() { return sizeof(T) == 4 ? 4 : 3; }
 
@@ -274,16 +315,25 @@ __device__ __forceinline__ cx<T> eighth(cx<T> w) {
 }
 
 // pass S (S >= 1) of a B-point transform, from the B-point table `tw`
-template <typename T, int B, int S, bool EXACT8>
-__device__ __forceinline__ void pass_twiddles(PassTw<T>& w, const cx<T>* __restrict__ tw, int tid) {
+constexpr int product_offset(int B, int s);
+
+template <typename T, int B, int S, int RND>
+__device__ __forceinline__ void pass_twiddles(TwOf<T, RND>& w, const cx<T>* __restrict__ tw, int tid) {
     constexpr int p = pass_span(B, S);
+    if constexpr (RND == SEVEN) {
+        const cx<T>* __restrict__ row = tw + product_offset(B, S) + (tid & (p - 1));
+#pragma unroll
+        for (int q = 0; q < 7; ++q) w.w[q] = row[q * p];
+        return;
+    } else {
     constexpr int stride = B / (p * 8);
     const int k = tid & (p - 1);
     w.w1 = tw[k * stride];
     w.w2 = tw[2 * k * stride];
     w.w4 = tw[4 * k * stride];
-    if constexpr (EXACT8) w.w8 = tw[(k + p) * stride];
+    if constexpr (RND != W8_FORMED) w.w8 = tw[(k + p) * stride];
     else w.w8 = eighth(w.w1);
+    }
 }
 
 // LDS twiddle table: pass s >= 1 (span p) holds w, w^2, w^4 and, in FP32,
@@ -314,7 +364,7 @@ __device__ __forceinline__ void fill_twiddle_table(cx<T>* tl, const cx<T>* __res
     }
 }
 
-// The table of TW_PRODUCTS: pass s >= 1 holds w^q, q = 1..7, in seven rows of p.
+// The table of TW_PRODUCTS, and a pass table: pass s >= 1 holds w^q, q = 1..7, in seven rows of p.
 constexpr int product_offset(int B, int s) {
     int o = 0;
     for (int t = 1; t < s; ++t) o += 7 * pass_span(B, t);
@@ -339,7 +389,7 @@ __device__ __forceinline__ void fill_product_table(cx<T>* tl, const cx<T>* __res
 template <typename T, int B, int S, int NP>
 __device__ __forceinline__ void all_twiddles(PassTw<T> (&w)[NP - 1], const cx<T>* __restrict__ tw, int tid) {
     if constexpr (S < NP) {
-        pass_twiddles<T, B, S, sizeof(T) == 4>(w[S - 1], tw, tid);
+        pass_twiddles<T, B, S, rounding<T>()>(w[S - 1], tw, tid);
         all_twiddles<T, B, S + 1, NP>(w, tw, tid);
     }
 }
@@ -405,14 +455,14 @@ __device__ __forceinline__ void pass_first(const cx<T> (&v)[8], cx<T>* out, int 
     }
 }
 
-template <typename T, int B, int SIGN, int S, int NP, bool DBUF, int TWS, bool LEAN, bool EXACT8, bool SC>
-__device__ __forceinline__ void passes(cx<T> (&v)[8], cx<T>* buf0, cx<T>* buf1, PassTw<T> (&wall)[NP - 1],
+template <typename T, int B, int SIGN, int S, int NP, bool DBUF, int TWS, bool LEAN, int RND, bool SC>
+__device__ __forceinline__ void passes(cx<T> (&v)[8], cx<T>* buf0, cx<T>* buf1, TwOf<T, RND> (&wall)[NP - 1],
                                        const cx<T>* __restrict__ tw, const cx<T>* tl, int tid, const T* f) {
     if constexpr (TWS == TW_AHEAD) {
         int t = tid;
         asm volatile("" : "+v"(t));          // loaded here, not earlier
-        if constexpr (S == 0) pass_twiddles<T, B, 1, EXACT8>(wall[0], tw, t);
-        if constexpr (S + 2 < NP) pass_twiddles<T, B, S + 2, EXACT8>(wall[S + 1], tw, t);
+        if constexpr (S == 0) pass_twiddles<T, B, 1, RND>(wall[0], tw, t);
+        if constexpr (S + 2 < NP) pass_twiddles<T, B, S + 2, RND>(wall[S + 1], tw, t);
     }
     constexpr int p = pass_span(B, S);
     constexpr bool first = (S == 0), last = (S == NP - 1);
@@ -433,7 +483,7 @@ __device__ __forceinline__ void passes(cx<T> (&v)[8], cx<T>* buf0, cx<T>* buf1, 
             for (int m = 0; m < 8; ++m) asm volatile("" : "+v"(v[m].re), "+v"(v[m].im));
             __syncthreads();
         }
-        PassTw<T> w;
+        TwOf<T, RND> w;
         if constexpr (TWS == TW_PRODUCTS) {
             int k = tid & (p - 1);
             asm volatile("" : "+v"(k));      // read here, not hoisted out of the caller's loops
@@ -449,8 +499,8 @@ __device__ __forceinline__ void passes(cx<T> (&v)[8], cx<T>* buf0, cx<T>* buf1, 
         } else if constexpr (TWS == TW_PASS) {
             int t = tid;
             asm volatile("" : "+v"(t));      // loaded here, not earlier
-            pass_twiddles<T, B, S, EXACT8>(w, tw, t);
-        } else {
+            pass_twiddles<T, B, S, RND>(w, tw, t);
+        } else if constexpr (RND != SEVEN) {
             int k = tid & (p - 1);
             asm volatile("" : "+v"(k));      // read here, not hoisted out of the caller's loops
             const cx<T>* row = tl + tl_offset<T>(B, S) + k;
@@ -464,7 +514,7 @@ __device__ __forceinline__ void passes(cx<T> (&v)[8], cx<T>* buf0, cx<T>* buf1, 
         else dft8_tw<SIGN>(v, w);
         if constexpr (!last) pass_write<T, B, S, LEAN>(v, out, tid);
     }
-    if constexpr (!last) passes<T, B, SIGN, S + 1, NP, DBUF, TWS, LEAN, EXACT8, SC>(v, buf0, buf1, wall, tw, tl, tid, f);
+    if constexpr (!last) passes<T, B, SIGN, S + 1, NP, DBUF, TWS, LEAN, RND, SC>(v, buf0, buf1, wall, tw, tl, tid, f);
 }
 
 // B-point transform of the workgroup's registers (see the file comment); must
@@ -482,19 +532,20 @@ __device__ __forceinline__ void passes(cx<T> (&v)[8], cx<T>* buf0, cx<T>* buf1, 
 // `tw` holds exp(+2 pi i j / B), j = 0..B-1; `regs` for TW_REGS, `tl` for
 // TW_TABLE and TW_PRODUCTS.  LEAN: every access forms its LDS address (one operation) instead of
 // the caller's loop keeping it in a register, for callers that spill otherwise.
-template <typename T, int B, int SIGN, bool DBUF, int TWS, bool LEAN = false, bool EXACT8 = sizeof(T) == 4,
+template <typename T, int B, int SIGN, bool DBUF, int TWS, bool LEAN = false, int RND = rounding<T>(),
           bool SC = false>
 __device__ __forceinline__ void block_fft(cx<T> (&v)[8], cx<T>*& buf0, cx<T>*& buf1, const cx<T>* __restrict__ tw,
                                           int tid, const Twiddles<T, B>* regs = nullptr, const cx<T>* tl = nullptr,
                                           const T* f = nullptr) {
     static_assert((B & (B - 1)) == 0 && B >= 64, "power-of-two block of at least 64 points");
     constexpr int NP = n_passes(B);
-    PassTw<T> w[NP - 1];
+    static_assert(RND != SEVEN || TWS == TW_AHEAD || TWS == TW_PASS, "seven twiddles are loaded");
+    TwOf<T, RND> w[NP - 1];
     if constexpr (TWS == TW_REGS) {
 #pragma unroll
         for (int i = 0; i < NP - 1; ++i) w[i] = regs->w[i];
     }
-    passes<T, B, SIGN, 0, NP, DBUF, TWS, LEAN, EXACT8, SC>(v, buf0, buf1, w, tw, tl, tid, f);
+    passes<T, B, SIGN, 0, NP, DBUF, TWS, LEAN, RND, SC>(v, buf0, buf1, w, tw, tl, tid, f);
     if constexpr (DBUF && (NP - 1) % 2 == 1) {
         cx<T>* s = buf0;
         buf0 = buf1;
@@ -504,20 +555,20 @@ __device__ __forceinline__ void block_fft(cx<T> (&v)[8], cx<T>*& buf0, cx<T>*& b
 
 // The transform of v_m f_m (f real, one factor a point): half of the products
 // are fused into the first pass's additions (dft2_scaled).
-template <typename T, int B, int SIGN, bool DBUF, int TWS, bool LEAN = false, bool EXACT8 = sizeof(T) == 4>
+template <typename T, int B, int SIGN, bool DBUF, int TWS, bool LEAN = false, int RND = rounding<T>()>
 __device__ __forceinline__ void block_fft_scaled(cx<T> (&v)[8], const T (&f)[8], cx<T>*& buf0, cx<T>*& buf1,
                                                  const cx<T>* __restrict__ tw, int tid,
                                                  const Twiddles<T, B>* regs = nullptr, const cx<T>* tl = nullptr) {
-    block_fft<T, B, SIGN, DBUF, TWS, LEAN, EXACT8, true>(v, buf0, buf1, tw, tid, regs, tl, f);
+    block_fft<T, B, SIGN, DBUF, TWS, LEAN, RND, true>(v, buf0, buf1, tw, tid, regs, tl, f);
 }
 
 // ... with the same factor at every point
-template <typename T, int B, int SIGN, bool DBUF, int TWS, bool LEAN = false, bool EXACT8 = sizeof(T) == 4>
+template <typename T, int B, int SIGN, bool DBUF, int TWS, bool LEAN = false, int RND = rounding<T>()>
 __device__ __forceinline__ void block_fft_scaled(cx<T> (&v)[8], T s, cx<T>*& buf0, cx<T>*& buf1,
                                                  const cx<T>* __restrict__ tw, int tid,
                                                  const Twiddles<T, B>* regs = nullptr, const cx<T>* tl = nullptr) {
     const T f[8] = {s, s, s, s, s, s, s, s};
-    block_fft<T, B, SIGN, DBUF, TWS, LEAN, EXACT8, true>(v, buf0, buf1, tw, tid, regs, tl, f);
+    block_fft<T, B, SIGN, DBUF, TWS, LEAN, RND, true>(v, buf0, buf1, tw, tid, regs, tl, f);
 }
 
 // ---- two transforms side by side --------------------------------------------------

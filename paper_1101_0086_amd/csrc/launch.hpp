@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 #include <cstdint>
+#include <vector>
 
 namespace mpa {
 
@@ -142,8 +143,8 @@ struct WindowStepArgs {
     const void* phase;              // (M+1) x N node phasors e^{i beta_j}, spectral order (node precision)
     const void* phase_last;         // N FP64 node-M phasors (times the roll-off when blocked), spectral order
     const double* node_scale_host;  // host: c_j = e^{Gamma_j} / N, e_j = dz e^{-Gamma_j}, j = 0..M
-    const void* tw1; const void* tw1_64;   // N1 twiddles exp(+2 pi i j / N1), node precision / FP64
-    const void* tw2; const void* tw2_64;   // N2 twiddles
+    const void* tw1; const void* tw1_64;   // N1 twiddles exp(+2 pi i j / N1), node precision (FP32: a pass table) / FP64
+    const void* tw2; const void* tw2_64;   // N2 twiddles likewise
     const void* twl; const void* twh;      // w_N split tables, node precision
     const void* twl_64; const void* twh_64;
     void* psi0;                     // windows x N FP64 complex
@@ -158,6 +159,10 @@ struct WindowStepArgs {
 };
 
 hipError_t launch_window_step(const WindowStepArgs& w);
+// Pass table of an n-point transform (n = 64 .. 4096, interleaved re, im): its passes
+// with twiddles after each other, span p each: rows q = 1..7 of exp(2 pi i q k / (8 p)),
+// k = 0..p-1.
+std::vector<double> pass_table(int n);
 // Phase table in the row-pass order of the four-step transform (see
 // launch_phase_table for coef and the optional roll-off `mask`, with B = n1 n2).
 hipError_t launch_phase_table_t(void* table, int precision, int n1, int n2, int rows, const double* coef,

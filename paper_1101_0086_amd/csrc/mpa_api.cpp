@@ -657,9 +657,10 @@ static int create_plan(const mpa_params* params, const mpa_map* map, int device,
             const std::vector<double>& v = tabs[t];
             // the node-precision copy at index 2t (or 2t for tw1/tw2 and 4/5 for twl/twh), FP64 beside it
             const int ip = t < 2 ? 2 * t : 4 + (t - 2), i64 = t < 2 ? 2 * t + 1 : 6 + (t - 2);
+            const std::vector<double> vp = t < 2 && f32 ? mpa::pass_table(t == 0 ? p->n1 : p->n2) : v;
             wok = hipMalloc(&p->w_tw[i64], v.size() * 8) == hipSuccess &&
                   hipMemcpy(p->w_tw[i64], v.data(), v.size() * 8, hipMemcpyHostToDevice) == hipSuccess &&
-                  hipMalloc(&p->w_tw[ip], v.size() * rsz) == hipSuccess && upload_real(p->w_tw[ip], v);
+                  hipMalloc(&p->w_tw[ip], vp.size() * rsz) == hipSuccess && upload_real(p->w_tw[ip], vp);
         }
         wok = wok && hipMalloc(&p->w_psi0, NW * N * 16) == hipSuccess &&
               hipMalloc(&p->w_sums, (size_t)params->n_iter * NW * N * 16) == hipSuccess &&

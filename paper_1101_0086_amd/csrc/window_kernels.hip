@@ -36,8 +36,9 @@
 // cache, at 2^22 (FP64 psi_0 and sums, 200 MiB) it does not.  Long step, M = 4, two
 // sweeps, FP32, against row passes in and out of their own (3 n_iter M + 6), two
 // FP32 table gathers a point for w_N and column groups dealt round the XCDs:
-// 2^22 modes 1645 -> 803 us, 2^20 511 -> 241, 2^16 176 -> 104, 2^13 140 -> 93.
+// 2^22 modes 1645 -> 825 us, 2^20 511 -> 246, 2^16 176 -> 103, 2^13 140 -> 89.
 #include <algorithm>
+#include <cmath>
 #include <type_traits>
 
 #include "block_fft.hpp"
@@ -55,6 +56,15 @@ __device__ __forceinline__ cx<double> widen(cx<T> a) { return {double(a.re), dou
 
 template <typename T>
 __device__ __forceinline__ cx<T> narrow(cx<double> a) { return {T(a.re), T(a.im)}; }
+
+// FP32 transforms take seven twiddles a pass, from a pass table, whose rows a wave
+// reads contiguously.  With four (three rounded twiddles in a row) the error of a
+// field was 0.5 % larger after a few long steps (2^13 to 2^16 modes) and 7 to 12 % after
+// a strongly nonlinear one than with products of seven; now it is as with those.  Four
+// long steps of 2^20 modes 1003 us (978 with four; 1039 with seven gathered from the
+// N-point table, 1020 loaded at the start of each pass).
+template <typename T>
+constexpr int win_rounding() { return sizeof(T) == 4 ? SEVEN : W8_TABLE; }
 
 // w_N^{j} = twh[j >> split] twl[j mod 2^split], j = n2 k1 < N
 template <typename T>
@@ -139,7 +149,7 @@ win_cols_kernel(const cx<TIN>* __restrict__ src, cx<TOUT>* __restrict__ dst, int
             v[m] = cx<TK>{TK(x.re), TK(x.im)};
         }
     }
-    if constexpr (MODE == WC_NODE || MODE == WC_INV) block_fft<TK, N1, -1, DBUF, TW_AHEAD, false, true>(v, my, my1, tw1, t);
+    if constexpr (MODE == WC_NODE || MODE == WC_INV) block_fft<TK, N1, -1, DBUF, TW_AHEAD, false, win_rounding<TK>()>(v, my, my1, tw1, t);
     if constexpr (MODE != WC_INV) {
         if constexpr (MODE == WC_NODE) {
             TK f[R];
@@ -148,9 +158,9 @@ win_cols_kernel(const cx<TIN>* __restrict__ src, cx<TOUT>* __restrict__ dst, int
                 v[m] = scale(v[m], cnode);
                 f[m] = cube_factor(v[m], dnode);
             }
-            block_fft_scaled<TK, N1, +1, DBUF, TW_AHEAD, false, true>(v, f, my, my1, tw1, t);
+            block_fft_scaled<TK, N1, +1, DBUF, TW_AHEAD, false, win_rounding<TK>()>(v, f, my, my1, tw1, t);
         } else {
-            block_fft<TK, N1, +1, DBUF, TW_AHEAD, false, true>(v, my, my1, tw1, t);
+            block_fft<TK, N1, +1, DBUF, TW_AHEAD, false, win_rounding<TK>()>(v, my, my1, tw1, t);
         }
         Powers<TK> w(twl, twh, split, col, t, NT);
 #pragma unroll
@@ -206,7 +216,7 @@ win_rows_kernel(WinRowArgs a, const cx<T>* __restrict__ tw2, const cx<double>* _
         const cx<double>* src = static_cast<const cx<double>*>(a.src) + woff + base;
 #pragma unroll
         for (int m = 0; m < R; ++m) z[m] = src[NT * m];
-        block_fft<double, N2, +1, false, TW_AHEAD, false, true>(z, d0, d1, tw2_64, t);
+        block_fft<double, N2, +1, false, TW_AHEAD, false, W8_TABLE>(z, d0, d1, tw2_64, t);
 #pragma unroll
         for (int m = 0; m < R; ++m) {
             psi0[NT * m] = z[m];
@@ -216,7 +226,7 @@ win_rows_kernel(WinRowArgs a, const cx<T>* __restrict__ tw2, const cx<double>* _
         const cx<T>* src = static_cast<const cx<T>*>(a.src) + woff + base;
 #pragma unroll
         for (int m = 0; m < R; ++m) v[m] = src[NT * m];
-        block_fft<T, N2, +1, DBUF, TW_AHEAD, false, true>(v, b0, b1, tw2, t);
+        block_fft<T, N2, +1, DBUF, TW_AHEAD, false, win_rounding<T>()>(v, b0, b1, tw2, t);
     }
     cx<T>* u0 = static_cast<cx<T>*>(a.u0) + woff + base;
     if constexpr (MODE == WR_U0) {
@@ -247,7 +257,7 @@ win_rows_kernel(WinRowArgs a, const cx<T>* __restrict__ tw2, const cx<double>* _
         const cx<double>* pl = static_cast<const cx<double>*>(a.ph_last) + base;
 #pragma unroll
         for (int m = 0; m < R; ++m) z[m] = cmul(z[m], pl[NT * m]);
-        block_fft_scaled<double, N2, -1, false, TW_AHEAD, false, true>(z, a.out_scale, d0, d1, tw2_64, t);
+        block_fft_scaled<double, N2, -1, false, TW_AHEAD, false, W8_TABLE>(z, a.out_scale, d0, d1, tw2_64, t);
         cx<double>* dst = static_cast<cx<double>*>(a.dst) + woff + base;
         Powers<double> w(twl64, twh64, split, k1, t, NT);
 #pragma unroll
@@ -256,7 +266,7 @@ win_rows_kernel(WinRowArgs a, const cx<T>* __restrict__ tw2, const cx<double>* _
         const cx<T>* ph = static_cast<const cx<T>*>(a.ph_next) + base;
 #pragma unroll
         for (int m = 0; m < R; ++m) v[m] = cmul(v[m], ph[NT * m]);
-        block_fft<T, N2, -1, DBUF, TW_AHEAD, false, true>(v, b0, b1, tw2, t);
+        block_fft<T, N2, -1, DBUF, TW_AHEAD, false, win_rounding<T>()>(v, b0, b1, tw2, t);
         cx<T>* dst = static_cast<cx<T>*>(a.dst) + woff + base;
         Powers<T> w(twl64, twh64, split, k1, t, NT);
 #pragma unroll
@@ -419,6 +429,21 @@ static hipError_t window_step_t(const WindowStepArgs& w) {
                        static_cast<const cx<double>*>(w.work64), static_cast<cx<T>*>(w.out), (long long)w.n_field,
                        (int)w.n, w.core, w.lead);
     return hipGetLastError();
+}
+
+std::vector<double> pass_table(int n) {
+    std::vector<double> t(2 * (size_t)product_elems(n));
+    for (int s = 1; s < n_passes(n); ++s) {
+        const int p = pass_span(n, s);
+        for (int q = 1; q < 8; ++q)
+            for (int k = 0; k < p; ++k) {
+                const double a = 2.0 * 3.14159265358979323846 * (double(q * k) / (8 * p));
+                const size_t i = (size_t)product_offset(n, s) + (size_t)(q - 1) * p + k;
+                t[2 * i] = std::cos(a);
+                t[2 * i + 1] = std::sin(a);
+            }
+    }
+    return t;
 }
 
 hipError_t launch_window_step(const WindowStepArgs& w) {
