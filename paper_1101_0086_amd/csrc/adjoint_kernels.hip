@@ -114,10 +114,14 @@ __device__ __forceinline__ void node_fft_scaled(cx<T> (&v)[PTS], const F& f, cx<
 // table the kernel is held to 256 registers (two workgroups per CU at
 // B = 2048).  Each access forms its LDS address (LEAN): kept over the node
 // loop they spilled 64 to 90 registers at two sweeps.  The reverse half is a
-// chain of 13 transforms (M = 2, two sweeps) bound by their latency: its stored
+// chain of 13 transforms (M = 2, two sweeps) bound by their latency: in FP32 its stored
 // values are loaded a transform ahead of their use, and the derivatives'
 // omega^2, omega^3 are applied once at the end instead of at each evaluation
-// (54 to 33.5 us a launch of 43 blocks of 2048).
+// (54 to 33.5 us a launch of 43 blocks of 2048).  FP32 whole steps use
+// up to 36 bytes of scratch a lane at two sweeps and 144 at three; FP64 ones 160 to
+// 216 (104 in the reverse half alone) and 320 to 472.  FP64, 2^19 modes, two sweeps, us
+// a step with the loads ahead (584 bytes) and without: 512-blocks 159 / 115, 2048
+// 193 / 145; 2^15 modes, 2048 65 / 53.
 template <typename T, int B, int NIT, int PART>
 __global__ void __launch_bounds__(B / PTS) __attribute__((amdgpu_waves_per_eu(2)))
 mpa_adjoint_block_kernel(const cx<T>* __restrict__ fin, const cx<double>* __restrict__ gin,
