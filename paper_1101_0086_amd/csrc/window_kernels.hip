@@ -119,9 +119,11 @@ enum WinColMode { WC_FWD = 0, WC_FWD_CUBE = 1, WC_NODE = 2, WC_INV = 3 };
 // b mod 8), so that the groups that share a cache line of a row share that
 // XCD's L2; the columns' exchange buffers are offset so that the lanes the LDS
 // serves together (16 of 8 bytes, 8 of 16 bytes) meet distinct banks.
+// `dst` may be `src` (no restrict qualifier on either): a thread writes the
+// elements that it alone read.
 template <typename TIN, typename TK, typename TOUT, int N1, int TC, int MODE>
 __global__ void __launch_bounds__(TC * N1 / WP)
-win_cols_kernel(const cx<TIN>* __restrict__ src, cx<TOUT>* __restrict__ dst, int n2,
+win_cols_kernel(const cx<TIN>* src, cx<TOUT>* dst, int n2,
                 const cx<TK>* __restrict__ tw1, const cx<double>* __restrict__ twl,
                 const cx<double>* __restrict__ twh, int split, TK cnode, TK dnode) {
     constexpr int R = WP, NT = N1 / R;
