@@ -145,8 +145,7 @@ struct WindowStepArgs {
     const double* node_scale_host;  // host: c_j = e^{Gamma_j} / N, e_j = dz e^{-Gamma_j}, j = 0..M
     const void* tw1; const void* tw1_64;   // N1 twiddles exp(+2 pi i j / N1), node precision (FP32: a pass table) / FP64
     const void* tw2; const void* tw2_64;   // N2 twiddles likewise
-    const void* twl; const void* twh;      // w_N split tables, node precision
-    const void* twl_64; const void* twh_64;
+    const void* twl; const void* twh;      // w_N split tables, FP64
     void* psi0;                     // windows x N FP64 complex
     void* sums;                     // n_iter x windows x N FP64 complex
     void* cur;                      // windows x N complex (node precision)

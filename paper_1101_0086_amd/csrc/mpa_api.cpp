@@ -296,7 +296,7 @@ struct mpa_plan {
     // distributed gain with boundary-crossing steps: node-scale row of each (step table,
     // gain row) pair that occurs (the step's node sigma times the gain profile of its row)
     std::map<std::pair<int, int>, int> combo_row;
-    void* w_tw[8] = {};                 // tw1, tw1_64, tw2, tw2_64, twl, twh, twl_64, twh_64
+    void* w_tw[6] = {};                 // tw1, tw2, twl, twh in FP64; FP32 plans: pass tables of tw1, tw2
     void* w_psi0 = nullptr;
     void* w_sums = nullptr;
     void* w_cur = nullptr;
@@ -653,14 +653,12 @@ static int create_plan(const mpa_params* params, const mpa_map* map, int device,
                                              phasors(int64_t(1) << p->split, 1.0, (double)N),
                                              phasors(N >> p->split, (double)(int64_t(1) << p->split), (double)N)};
         bool wok = true;
-        for (int t = 0; t < 4 && wok; ++t) {
-            const std::vector<double>& v = tabs[t];
-            // the node-precision copy at index 2t (or 2t for tw1/tw2 and 4/5 for twl/twh), FP64 beside it
-            const int ip = t < 2 ? 2 * t : 4 + (t - 2), i64 = t < 2 ? 2 * t + 1 : 6 + (t - 2);
-            const std::vector<double> vp = t < 2 && f32 ? mpa::pass_table(t == 0 ? p->n1 : p->n2) : v;
-            wok = hipMalloc(&p->w_tw[i64], v.size() * 8) == hipSuccess &&
-                  hipMemcpy(p->w_tw[i64], v.data(), v.size() * 8, hipMemcpyHostToDevice) == hipSuccess &&
-                  hipMalloc(&p->w_tw[ip], vp.size() * rsz) == hipSuccess && upload_real(p->w_tw[ip], vp);
+        for (int t = 0; t < 4 && wok; ++t)
+            wok = hipMalloc(&p->w_tw[t], tabs[t].size() * 8) == hipSuccess &&
+                  hipMemcpy(p->w_tw[t], tabs[t].data(), tabs[t].size() * 8, hipMemcpyHostToDevice) == hipSuccess;
+        for (int t = 0; t < 2 && wok && f32; ++t) {
+            const std::vector<double> v = mpa::pass_table(t == 0 ? p->n1 : p->n2);
+            wok = hipMalloc(&p->w_tw[4 + t], v.size() * rsz) == hipSuccess && upload_real(p->w_tw[4 + t], v);
         }
         wok = wok && hipMalloc(&p->w_psi0, NW * N * 16) == hipSuccess &&
               hipMalloc(&p->w_sums, (size_t)params->n_iter * NW * N * 16) == hipSuccess &&
@@ -807,14 +805,12 @@ static int launch_long_step(mpa_plan* p, const void* in, void* out, int64_t m, h
         w.phase = a.phase;
         w.phase_last = a.phase_last;
         w.node_scale_host = p->ns_host.data() + (size_t)gain_row(p, m, s) * 2 * (M + 1);
-        w.tw1 = p->w_tw[0];
-        w.tw1_64 = p->w_tw[1];
-        w.tw2 = p->w_tw[2];
-        w.tw2_64 = p->w_tw[3];
-        w.twl = p->w_tw[4];
-        w.twh = p->w_tw[5];
-        w.twl_64 = p->w_tw[6];
-        w.twh_64 = p->w_tw[7];
+        w.tw1_64 = p->w_tw[0];
+        w.tw2_64 = p->w_tw[1];
+        w.twl = p->w_tw[2];
+        w.twh = p->w_tw[3];
+        w.tw1 = p->w_tw[4] ? p->w_tw[4] : w.tw1_64;
+        w.tw2 = p->w_tw[5] ? p->w_tw[5] : w.tw2_64;
         w.psi0 = p->w_psi0;
         w.sums = p->w_sums;
         w.cur = p->w_cur;

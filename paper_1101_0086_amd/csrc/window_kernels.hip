@@ -327,8 +327,8 @@ static hipError_t cols_n1(const WindowStepArgs& w, const void* src, void* dst, c
     if (w.n2 % TC) return hipErrorInvalidValue;
     hipLaunchKernelGGL((win_cols_kernel<TIN, TK, TOUT, N1, TC, MODE>), dim3(w.n2 / TC, w.windows), dim3(TC * N1 / WP), 0,
                        w.stream, static_cast<const cx<TIN>*>(src), static_cast<cx<TOUT>*>(dst), w.n2,
-                       static_cast<const cx<TK>*>(tw1), static_cast<const cx<double>*>(w.twl_64),
-                       static_cast<const cx<double>*>(w.twh_64), w.split, TK(cnode), TK(dnode));
+                       static_cast<const cx<TK>*>(tw1), static_cast<const cx<double>*>(w.twl),
+                       static_cast<const cx<double>*>(w.twh), w.split, TK(cnode), TK(dnode));
     return hipGetLastError();
 }
 
@@ -352,7 +352,7 @@ static hipError_t rows_n2(const WindowStepArgs& w, const WinRowArgs& a) {
     if (w.n1 % TR) return hipErrorInvalidValue;
     hipLaunchKernelGGL((win_rows_kernel<T, N2, TR, MODE>), dim3(w.n1 / TR, w.windows), dim3(TR * N2 / WP), 0, w.stream, a,
                        static_cast<const cx<T>*>(w.tw2), static_cast<const cx<double>*>(w.tw2_64),
-                       static_cast<const cx<double>*>(w.twl_64), static_cast<const cx<double>*>(w.twh_64), w.split,
+                       static_cast<const cx<double>*>(w.twl), static_cast<const cx<double>*>(w.twh), w.split,
                        (long long)w.n);
     return hipGetLastError();
 }
