@@ -989,6 +989,45 @@ static AdjTarget single_target(mpa_plan* p) {
     return {p, nullptr, nullptr, 0, p->prm.n, p->n_blocks, p->n_blocks, p->work, &p->adj};
 }
 
+// Bytes of one node store (AdjWork::node and last) of a work item.
+static size_t store_bytes(const mpa_plan* p) {
+    return (size_t)p->block * ((size_t)p->prm.n_iter * p->prm.M * 3 * p->elem + 16);
+}
+
+// Node stores for `count` items, or neither of the two buffers.
+static bool alloc_stores(const AdjTarget& t, size_t count) {
+    AdjWork* w = t.w;
+    const size_t last = count * (size_t)t.p->block * 16;
+    if (hipMalloc(&w->node, count * store_bytes(t.p) - last) == hipSuccess && hipMalloc(&w->last, last) == hipSuccess)
+        return true;
+    for (void** q : {&w->node, &w->last}) {
+        if (*q) (void)hipFree(*q);
+        *q = nullptr;
+    }
+    (void)hipGetLastError();
+    return false;
+}
+
+// Device memory for a part of the reverse pass.  Where it is short, the stores that
+// several steps' recomputes share are given back first: the one-launch form, which
+// needs less, takes what it took before there was the other.
+static bool alloc_part(const AdjTarget& t, void** buf, size_t bytes) {
+    if (hipMalloc(buf, bytes) == hipSuccess) return true;
+    *buf = nullptr;
+    (void)hipGetLastError();
+    AdjWork* w = t.w;
+    if (!w->node || w->ahead <= 1) return false;
+    (void)hipDeviceSynchronize();
+    (void)hipFree(w->node);
+    (void)hipFree(w->last);
+    w->node = w->last = nullptr;
+    w->ahead = 1;
+    if (alloc_stores(t, (size_t)t.grid) && hipMalloc(buf, bytes) == hipSuccess) return true;
+    *buf = nullptr;
+    (void)hipGetLastError();
+    return false;
+}
+
 // Grow-only device buffer of `count` fields.
 static int reserve_fields(const AdjTarget& t, void** buf, int64_t* cap, int64_t count) {
     if (count <= *cap) return MPA_OK;
@@ -998,8 +1037,7 @@ static int reserve_fields(const AdjTarget& t, void** buf, int64_t* cap, int64_t 
         *buf = nullptr;
         *cap = 0;
     }
-    if (hipMalloc(buf, (size_t)count * t.count * t.p->elem) != hipSuccess) {
-        *buf = nullptr;
+    if (!alloc_part(t, buf, (size_t)count * t.count * t.p->elem)) {
         return fail(MPA_ENOMEM, "adjoint: allocation of %lld fields failed", (long long)count);
     }
     *cap = count;
@@ -1030,35 +1068,18 @@ static int recompute_ahead(const mpa_plan* p, int64_t n_items, size_t per_store)
 static int adjoint_setup(const AdjTarget& t) {
     mpa_plan* p = t.p;
     AdjWork* w = t.w;
-    const int B = p->block, M = p->prm.M, nit = p->prm.n_iter, S = (int)p->beta2.size();
+    const int B = p->block, M = p->prm.M, S = (int)p->beta2.size();
     if (!w->node) {
         const size_t ni = (size_t)t.n_items;
-        size_t wg = (size_t)t.grid;
-        const size_t per_store = (size_t)B * ((size_t)nit * M * 3 * p->elem + 16);
-        const auto stores = [&]() {
-            return hipMalloc(&w->node, wg * nit * M * 3 * B * p->elem) == hipSuccess &&
-                   hipMalloc(&w->last, wg * B * 16) == hipSuccess;
-        };
-        w->ahead = recompute_ahead(p, t.n_items, per_store);
-        bool ok = false;
-        if (w->ahead > 1) {
-            wg = (size_t)w->ahead * ni;
-            ok = stores();
-            if (!ok) {                                // the one-launch form needs less
-                for (void** q : {&w->node, &w->last}) {
-                    if (*q) (void)hipFree(*q);
-                    *q = nullptr;
-                }
-                (void)hipGetLastError();
-                w->ahead = 1;
-                wg = (size_t)t.grid;
-            }
-        }
-        ok = (ok || stores()) &&
-                        hipMalloc(&w->gblk, ni * B * 16) == hipSuccess &&
-                        hipMalloc(&w->partial, ni * 3 * sizeof(double)) == hipSuccess &&
-                        hipMalloc(&w->ga, (size_t)t.count * 16) == hipSuccess &&
-                        hipMalloc(&w->gb, (size_t)t.count * 16) == hipSuccess;
+        // the parts that every form needs first: what fails where memory is short is then
+        // the larger stores, and the smaller ones are taken instead
+        bool ok = (w->gblk || hipMalloc(&w->gblk, ni * B * 16) == hipSuccess) &&
+                  (w->partial || hipMalloc(&w->partial, ni * 3 * sizeof(double)) == hipSuccess) &&
+                  (w->ga || hipMalloc(&w->ga, (size_t)t.count * 16) == hipSuccess) &&
+                  (w->gb || hipMalloc(&w->gb, (size_t)t.count * 16) == hipSuccess);
+        w->ahead = recompute_ahead(p, t.n_items, store_bytes(p));
+        if (ok && w->ahead > 1 && !alloc_stores(t, (size_t)w->ahead * ni)) w->ahead = 1;
+        ok = ok && (w->ahead > 1 || alloc_stores(t, (size_t)t.grid));
         if (!ok) {
             w->release();
             return fail(MPA_ENOMEM, "adjoint: workspace allocation failed");
@@ -1091,7 +1112,7 @@ static int adjoint_setup(const AdjTarget& t) {
                     e[2] = st.len[q][j];
                 }
         void* d = nullptr;
-        if (hipMalloc(&d, nw.size() * 8) != hipSuccess) return fail(MPA_ENOMEM, "adjoint: table allocation failed");
+        if (!alloc_part(t, &d, nw.size() * 8)) return fail(MPA_ENOMEM, "adjoint: table allocation failed");
         if (hipMemcpy(d, nw.data(), nw.size() * 8, hipMemcpyHostToDevice) != hipSuccess) {
             (void)hipFree(d);
             return fail(MPA_EDEVICE, "adjoint: node weight table upload failed");
@@ -1140,7 +1161,7 @@ static int adjoint_setup(const AdjTarget& t) {
             for (size_t q = 0; q < st.spans.size(); ++q)
                 fill(st.adj_row + (int)q, st.b2[M] / p->prm.L, st.b3[M] / p->prm.L, st.len[q][M] / p->prm.L);
         void* d = nullptr;
-        if (hipMalloc(&d, tab.size() * 8) != hipSuccess) return fail(MPA_ENOMEM, "adjoint: table allocation failed");
+        if (!alloc_part(t, &d, tab.size() * 8)) return fail(MPA_ENOMEM, "adjoint: table allocation failed");
         if (hipMemcpy(d, tab.data(), tab.size() * 8, hipMemcpyHostToDevice) != hipSuccess) {
             (void)hipFree(d);
             return fail(MPA_EDEVICE, "adjoint: roll-off derivative table upload failed");
