@@ -389,12 +389,12 @@ __device__ __forceinline__ void fill_product_table(cx<T>* tl, const cx<T>* __res
 template <typename T, int B, int S, int NP>
 __device__ __forceinline__ void all_twiddles(PassTw<T> (&w)[NP - 1], const cx<T>* __restrict__ tw, int tid) {
     if constexpr (S < NP) {
-        pass_twiddles<T, B, S, rounding<T>()>(w[S - 1], tw, tid);
+        pass_twiddles<T, B, S, W8_TABLE>(w[S - 1], tw, tid);
         all_twiddles<T, B, S + 1, NP>(w, tw, tid);
     }
 }
 
-// twiddles of every pass for TW_REGS
+// twiddles of every pass for TW_REGS, all from the table
 template <typename T, int B>
 struct Twiddles {
     PassTw<T> w[n_passes(B) - 1];
