@@ -48,6 +48,7 @@ struct BlockStepArgs {
     int32_t precision;       // 0: FP32 field / 1: FP64
     const BatchItems* batch; // nullptr for a single field
     const NodeBuffers* nodes;// node-parallel schedule (single field); nullptr: fused wavefront kernel
+    int32_t cus = 0;         // node-parallel schedule: compute units of the device
     hipStream_t stream;
     // node-parallel march of one full window: psi_0 of this step is in place (the step
     // before computed it); compute the next step's psi_0 at the end
@@ -57,7 +58,8 @@ struct BlockStepArgs {
 bool block_step_supported(int precision, int block, int n_iter);
 int threads_per_block(int precision, int block);
 hipError_t launch_block_step(const BlockStepArgs& a);
-// The same long step as n_iter + 2 launches in the node-parallel schedule (a.nodes != nullptr).
+// The same long step in the node-parallel schedule (a.nodes != nullptr): a first launch (none
+// when psi0_ready), n_iter sweeps, as many launches of sums where those are apart, and a last one.
 hipError_t launch_node_parallel_step(const BlockStepArgs& a);
 hipError_t launch_copy_field(const void* src, void* dst, int64_t count, int precision, hipStream_t stream);
 

@@ -217,6 +217,12 @@ int check_device(int device) {
     return MPA_OK;
 }
 
+int compute_units(int device) {
+    int cus = 0;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || cus <= 0) cus = 256;
+    return cus;
+}
+
 struct DevBuf {
     void* p = nullptr;
     ~DevBuf() {
@@ -268,6 +274,7 @@ struct AdjWork {
 struct mpa_plan {
     mpa_params prm{};
     int device = 0;
+    int cus = 256;                      // compute units of the device
     int block = 0, halo = 0, core = 0, n_blocks = 0;
     int shift = 0;                      // window shift (samples): windows start at b C - halo - shift
     size_t elem = 8;                    // bytes per complex sample
@@ -438,11 +445,15 @@ int mpa_plan_validate(const mpa_params* params, const mpa_map* map) {
 // fused kernel puts a block's n_iter M node evaluations one after another on
 // one CU, so with few blocks most of the chip is idle; the node-parallel
 // launches cost about as much as the evaluations of three nodes a sweep.
-// Measured per long step, fused against node-parallel, 4096-point blocks: FP64,
-// M = 4, two sweeps, 1 block 57 / 32 us, 16 blocks 58 / 34, 128 blocks 60 / 78;
-// M = 2, 1 block 34 / 30; M = 16, three sweeps, 1 block 302 / 52, 32 blocks
-// 306 / 121; FP32, M = 8, two sweeps, 1 block 61 / 34, 16 blocks 62 / 37, 128
-// blocks 62 / 80.  1024 node workgroups bound the state to 128 MiB.
+// Measured per long step, fused against node-parallel, over B = 512 .. 4096, one to
+// five sweeps, M = 2 .. 64 and 1 to 64 blocks in both precisions: every plan that the
+// rule takes is faster, the least 1.13 times (FP32, 4096 points, M = 16, 64 blocks, two
+// sweeps, 98.7 / 87.6 us).  At its edge: FP32, M = 8, one sweep, 512 points 14.8 / 8.6
+// with one block and 15.6 / 11.5 with 32, 4096 points and two sweeps 54.5 / 32.0 and
+// 55.3 / 41.2; FP64, M = 4, 512 points, one sweep 11.7 / 8.0 and, 16 blocks, 12.4 / 10.6,
+// 4096 points, two sweeps 48.8 / 30.2 and 49.5 / 34.0; M = 16, three sweeps, 1 block
+// 267 / 51, 32 blocks 271 / 123.  Below it: FP32, M = 4, 16 blocks of 512 10.3 / 10.4; FP64,
+// M = 2, 4 blocks of 512 8.6 / 9.7.  1024 node workgroups bound the state to 128 MiB.
 static bool nodes_fill_better(const mpa_params* prm, int n_blocks, bool window) {
     const int64_t M = prm->M;
     return prm->schedule == MPA_WAVEFRONT && !window && M >= (prm->precision == MPA_C64 ? 8 : 4) &&
@@ -464,6 +475,7 @@ static int create_plan(const mpa_params* params, const mpa_map* map, int device,
     auto* p = new mpa_plan();
     p->prm = *params;
     p->device = device;
+    p->cus = compute_units(device);
     p->sched = sched;
     const bool full = (params->block == 0 || (params->block == params->n && params->halo == 0));
     p->block = full ? (int)params->n : params->block;
@@ -782,6 +794,7 @@ static int launch_long_step(mpa_plan* p, const void* in, void* out, int64_t m, h
     a.precision = p->prm.precision;
     a.batch = batch;
     a.nodes = (batch == nullptr && p->nodes.psi0) ? &p->nodes : nullptr;
+    a.cus = p->cus;
     a.psi0_ready = psi0_ready;
     a.next_psi0 = next_psi0;
     a.stream = stream;
@@ -1054,11 +1067,8 @@ static int reserve_fields(const AdjTarget& t, void** buf, int64_t* cap, int64_t 
 // steps.  Under four steps to a launch the second launch and the stores' trip
 // through the cache leave little of that.
 static int recompute_ahead(const mpa_plan* p, int64_t n_items, size_t per_store) {
-    int cus = 0;
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, p->device) != hipSuccess || cus <= 0)
-        cus = 256;
     const int per_cu = mpa::adjoint_workgroups_per_cu(p->prm.precision, p->block, p->prm.n_iter);
-    const int64_t resident = (int64_t)cus * (per_cu > 0 ? per_cu : 1);
+    const int64_t resident = (int64_t)p->cus * (per_cu > 0 ? per_cu : 1);
     const int64_t fit = (int64_t)(((size_t)128 << 20) / (per_store * (size_t)n_items));
     const int64_t q = std::min<int64_t>({16, resident / n_items, fit});
     return q >= 4 ? (int)q : 1;
@@ -1620,8 +1630,7 @@ int mpa_batch_plan_create(const mpa_params* params, const mpa_map* map, const mp
         }
     }
     const int n_items = (int)(items.size() / 2);
-    int cus = 0;
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || cus <= 0) cus = 256;
+    const int cus = b->base->cus;
     bool ok = hipMalloc(&b->d_items, items.size() * sizeof(int)) == hipSuccess &&
               hipMalloc(&b->d_offset, b->offset.size() * 8) == hipSuccess &&
               hipMalloc(&b->d_len, b->len.size() * 8) == hipSuccess &&
@@ -1678,12 +1687,9 @@ static int adjoint_grid(mpa_batch_plan* b) {
     if (b->adj_grid) return b->adj_grid;
     const mpa_plan* p = b->base;
     const int n = b->items.n_items;
-    int cus = 0;
     (void)hipSetDevice(p->device);
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, p->device) != hipSuccess || cus <= 0)
-        cus = 256;
     const int per_cu = mpa::adjoint_workgroups_per_cu(p->prm.precision, p->block, p->prm.n_iter);
-    const int slots = cus * (per_cu > 0 ? per_cu : 1);
+    const int slots = p->cus * (per_cu > 0 ? per_cu : 1);
     const int rounds = (n + slots - 1) / slots;
     b->adj_grid = (n + rounds - 1) / rounds;
     return b->adj_grid;

@@ -38,7 +38,6 @@ namespace {
 
 constexpr int PTS = 8;
 constexpr int XCDS = 8;
-constexpr int NODE_DBUF_GROUPS = 256;   // workgroups up to which each has a CU of its own
 
 template <typename T>
 __device__ __forceinline__ cx<double> widen(cx<T> a) { return {double(a.re), double(a.im)}; }
@@ -287,10 +286,15 @@ static void launch_sweep(const BlockStepArgs& a, const NodeBuffers& nb, const vo
 // Whether Eq. 6's sums get a launch of their own.  A node's workgroup that adds
 // up its own prefix reads up to M rows through one CU's path to L2, which a
 // launch of one thread per frequency spreads over the chip.  Measured per long
-// step of three sweeps, own against apart: one block of 4096, M = 16, FP32 55.9 /
-// 45.3 us, FP64 60.0 / 52.2; M = 8 44.8 / 42.2, 47.5 / 46.8; four blocks, M = 16
-// 58.7 / 50.1, 62.6 / 61.0; sixteen 65.6 / 71.6, 80.4 / 85.9; one block of 1024,
-// M = 32 37.2 / 39.3, 38.8 / 40.8.
+// step, own against apart, B = 512 .. 4096, M = 4 .. 128, 1 to 16 blocks, one and
+// three sweeps, both precisions: where the rule takes the sums apart that is 0.985 to
+// 3.4 times as fast (1.41 on the average; one block of 4096, M = 16, three sweeps, FP32
+// 55.8 / 43.9 us, FP64 59.1 / 51.9; four blocks 58.2 / 49.6, 62.0 / 61.9; 512 points, M = 128
+// 78.2 / 58.6, 75.2 / 62.4).  The product M B stands for the bytes that one CU reads, and the
+// line is where no plan loses: at half of it FP64 loses up to 15 % (2048 points, M = 16,
+// eight blocks 40.7 / 47.0) and FP32 gains up to 13 % or loses up to 8 % (512 points, M = 64
+// 44.7 / 39.9; 4096, M = 8 43.6 / 40.3; 1024, M = 32, eight blocks 38.6 / 42.0); sixteen blocks of
+// 4096 lose at M = 16 (64.3 / 71.4) and would gain at M = 32 (121 / 88).
 static bool sums_apart(const BlockStepArgs& a) {
     const long long longest = (long long)a.M * a.block;
     return longest >= 65536 && a.n_blocks <= longest / 16384;
@@ -307,7 +311,7 @@ static hipError_t node_step_typed(const BlockStepArgs& a) {
     // more it is computed with psi_0 (2^19 modes, 1024 blocks of 2048, M = 1, two sweeps:
     // 66.7 us a long step as node 0, where every workgroup fills its twiddle table first,
     // 59 with psi_0)
-    const bool few = a.n_blocks <= NODE_DBUF_GROUPS;
+    const bool few = a.n_blocks <= a.cus;
     const int first = few ? 0 : 1;
     const auto init = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3(a.n_blocks), threads, 0, a.stream, static_cast<const cx<T>*>(a.in), psi0,
@@ -321,7 +325,7 @@ static hipError_t node_step_typed(const BlockStepArgs& a) {
     }
     const long long total = (long long)a.n_blocks * B;
     const dim3 sum_groups((unsigned)((total + SUM_TPB - 1) / SUM_TPB));
-    const bool dbuf = (long long)a.n_blocks * (a.M + 1) <= NODE_DBUF_GROUPS;
+    const bool dbuf = (long long)a.n_blocks * (a.M + 1) <= a.cus;
     const bool apart = sums_apart(a);
     for (int s = 0; s < a.n_iter; ++s) {
         // increments alternate between the two buffers, or (sums apart) the first holds
