@@ -15,8 +15,10 @@
 // d beta_j / d beta3 = omega^3 z_j / 6 (z_j = j dz from the long step start).
 //
 // One workgroup per block, as in the forward kernel.  The kernel first
-// repeats the block's forward long step with the same operations and keeps,
-// for every sweep s and node l >= 1, the node's time field A, its spectrum
+// repeats the block's forward long step (the same sums in the same order; its
+// transforms multiply by table twiddles and c_l, d_l are applied one by one, so
+// node values differ from the forward's in the last bits of the node precision)
+// and keeps, for every sweep s and node l >= 1, the node's time field A, its spectrum
 // y = psi e^{i beta_l} and the sigma-free increment U / sigma in a per-block
 // store in device memory (written and read back by the same workgroup).  The
 // reverse pass then visits the nodes from M down to 1 and, at each node, the

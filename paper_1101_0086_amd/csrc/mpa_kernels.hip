@@ -69,8 +69,8 @@ struct StepTables {
 
 // One field: one workgroup per block (`out` may be `in` when there is one block:
 // every read of it precedes the workgroup's first transform).  Bound by the
-// instructions of its 19 dependent transforms (M = 4, two sweeps) and the
-// exchange latency that two waves per SIMD leave open.  2^22 modes, 2048 blocks of 4096, 8 long steps:
+// instructions of its 19 transforms (M = 4, two sweeps; in pairs 12 one after
+// another) and the exchange latency that two waves per SIMD leave open.  2^22 modes, 2048 blocks of 4096, 8 long steps:
 // 2.62 ms with 8-point DFTs behind seven twiddle products and the last node
 // selected per element, 2.29 ms with the passes of block_fft.hpp, the last
 // node behind a uniform branch and the node's two scales folded (1446 against
