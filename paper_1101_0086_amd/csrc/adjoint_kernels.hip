@@ -120,7 +120,7 @@ __device__ __forceinline__ void node_fft_scaled(cx<T> (&v)[PTS], const F& f, cx<
 // values are loaded a transform ahead of their use, and the derivatives'
 // omega^2, omega^3 are applied once at the end instead of at each evaluation
 // (54 to 33.5 us a launch of 43 blocks of 2048).  FP32 whole steps use
-// up to 36 bytes of scratch a lane at two sweeps and 144 at three; FP64 ones 160 to
+// 72 to 104 bytes of scratch a lane at two sweeps and 168 to 192 at three; FP64 ones 160 to
 // 216 (104 in the reverse half alone) and 320 to 472.  FP64, 2^19 modes, two sweeps, us
 // a step with the loads ahead (584 bytes) and without: 512-blocks 159 / 115, 2048
 // 193 / 145; 2^15 modes, 2048 65 / 53.
